@@ -43,7 +43,12 @@ lbm_status validate(const lbm_params& p);
 // Eq. 10 argument 2 (P_EOS - rho/3) / G at its initial temperature.
 lbm_status check_initial(const lbm_params& p, const double* rho0);
 int default_seg_rows(const lbm_params& p, int rows, int min_rows = 2);
-void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, lbmk::Grid& g);
+// The tile shape a channel stepped alone takes by default (kTileNone: the
+// march, with default_seg_rows).
+int default_tile(const lbm_params& p, int rows);
+// Grid of a launch shape; a tile shape brings its own seg_rows.
+void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, lbmk::Grid& g,
+               int tile = lbmk::kTileNone);
 void fill_phys(const lbm_params& p, lbmk::Phys& k);
 
 }  // namespace lbmhost

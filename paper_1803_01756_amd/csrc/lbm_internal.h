@@ -16,6 +16,16 @@ constexpr int kLanes = 64;
 constexpr int kHalo = 5;
 constexpr int kOwned = kLanes - 2 * kHalo;
 
+// Launch shapes of the step.  kTileNone: every wave marches over a segment of
+// seg_rows rows.  The others: a workgroup of `waves` waves with `rows` rows
+// each holds a tile of up to rows x waves - 2 kHalo rows and its halo.
+struct TileShape {
+    int rows, waves;
+    constexpr int own() const { return rows * waves - 2 * kHalo; }
+};
+enum { kTileNone = 0, kTileFlat, kTileMid, kTileWide, kTileTall, kTileCount };
+constexpr TileShape kTiles[kTileCount] = {{0, 0}, {1, 16}, {3, 8}, {4, 8}, {2, 16}};
+
 // Constants that enter arithmetic done in the storage precision R, given in
 // R on the host so that the kernels never convert them per use.
 template <class R>
@@ -69,6 +79,7 @@ struct Grid {
     int frame_t;       // T held at T_w on the frame: outermost columns (and rows if periodic_y)
     int frame_rho;     // the frame is a reservoir at rest with density rho_frame
     int open_x;        // Zou-He pressure inlet at x = 0, outlet at x = Nx-1
+    int tile;          // launch shape (kTile...)
     int n_strips, n_segs, seg_rows, n_units, n_blocks_pad;
     unsigned plane;    // rows * pitch
 };

@@ -500,8 +500,9 @@ struct RealOf<double> {
 // Open ends: the inlet density at time level n, the vapour-branch root of
 // P_EOS(rho, T_in) = p0 (1 + p_amp sin(2 pi n / p_period)) (constant
 // p0 (1 + p_amp) when p_period <= 0).  Safeguarded Newton from rho_v inside
-// (0, rho_sp), rho_sp the vapour spinodal: a fixed number of iterations, so
-// a channel gets the same bits alone and in a batch.
+// (0, rho_sp), rho_sp the vapour spinodal; every lane takes the same number
+// of iterations (5 to 8), so a channel gets the same bits alone and in a batch.
+// 60 fixed iterations took some 9 us of the step's critical path (1600 x 48).
 __device__ double inlet_density(const Phys& k, long long n) {
     const double T = k.T_in_eos;
     const double target = k.p_period > 0.0
@@ -525,6 +526,7 @@ __device__ double inlet_density(const Phys& k, long long n) {
         }
         if (P < target) lo = r; else hi = r;
         double rn = r - (P - target) / dP;
+        if (fabs(rn - r) <= 4.5e-16 * r) return rn;  // at the root to rounding
         if (!(rn > lo && rn < hi)) rn = 0.5 * (lo + hi);
         r = rn;
     }
@@ -1145,6 +1147,378 @@ void step_kernel_f64(Grid g, Phys k,
     step_unit<double, false, kExt>(g, k, B, drive_at(k, n), rin, unit);
 }
 
+// ---- the tile step ------------------------------------------------------------
+// The march's time on a small grid is the length of one wave's way: seg_rows
+// + 10 row iterations one after another, 1.4 us each, however idle the chip
+// is.  Here a workgroup takes a tile of 54 columns x seg_rows rows: kWaves
+// waves of kRows consecutive rows each hold the tile and its five-row halo,
+// one column per lane.  Every stage runs on all rows of the tile before the
+// next begins; columns come from the adjacent lanes (DPP), the rows above and
+// below a wave's own through LDS, one barrier per stage.  The arithmetic per
+// node is the march's, expression by expression, so the results are too.
+// Measured (us per step, march / tile): 128 x 32 17.8 / 5.8, 300 x 100
+// 18.0 / 6.1, 2048 x 256 31.0 / 16.9, the last in FP64 51.6 / 30.1.  A small
+// grid is bound by the chain of stages and the launch (about 2 us), a
+// middling one by the halo's extra arithmetic.
+template <class R, int kWaves, bool kExt>
+struct TileLds {
+    double psi[kWaves][2][kLanes];
+    R drive;
+    R tn[kWaves][2][kLanes];
+    R ux[kWaves][2][kLanes], uy[kWaves][2][kLanes];
+    R st[3][kWaves][2][kLanes];
+    R lam[kExt ? kWaves : 1][2][kLanes];
+};
+
+template <class S, bool kMX, bool kExt, int kRows, int kWaves>
+__device__ __forceinline__ void tile_unit(const Grid& g, const Phys& k, const Bufs<S>& B,
+                                          long long n, int unit,
+                                          TileLds<typename RealOf<S>::T, kWaves, kExt>& L) {
+    using R = typename RealOf<S>::T;
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int strip = unit % g.n_strips;
+    const int seg = unit / g.n_strips;
+
+    int cx = strip * kOwned - kHalo + lane;
+    if (g.Nx >= kLanes) {  // at most one turn: -kHalo <= cx < Nx + kLanes
+        cx += cx < 0 ? g.Nx : (cx >= g.Nx ? -g.Nx : 0);
+    } else {
+        cx %= g.Nx;
+        if (cx < 0) cx += g.Nx;
+    }
+    const unsigned x = (unsigned)cx;
+    const unsigned xm = (unsigned)(cx == 0 ? g.Nx - 1 : cx - 1);
+    const unsigned xp = (unsigned)(cx == g.Nx - 1 ? 0 : cx + 1);
+    const int own_w = min(kOwned, g.Nx - strip * kOwned);
+    const bool own_lane = lane >= kHalo && lane < kHalo + own_w;
+    const int c0 = strip * kOwned;
+    auto moved = [&](const int b, const int b_next) {
+        constexpr int cpc = 64 / (int)sizeof(S), kMove = kHalo - 1;
+        const int r = b % cpc;
+        if (r == 0) return b;
+        if (r <= kMove) return b - r;
+        if (cpc - r <= kMove && b + (cpc - r) <= b_next) return b + (cpc - r);
+        return b;
+    };
+    const int st_lo = strip > 0 ? moved(c0, c0 + own_w) : 0;
+    const int st_hi = strip + 1 < g.n_strips ? moved(c0 + kOwned, min(c0 + 2 * kOwned, g.Nx))
+                                             : c0 + own_w;
+    const bool store_lane = c0 - kHalo + lane >= st_lo && c0 - kHalo + lane < st_hi;
+
+    const bool edge_col = cx == 0 || cx == g.Nx - 1;
+    auto on_frame = [&](const RowK& r) {
+        return edge_col || (g.periodic_y && (r.sr == 0 || r.sr == g.rows - 1));
+    };
+    const bool open_x = kExt && g.open_x != 0;
+    const bool at_in = open_x && cx == 0, at_out = open_x && cx == g.Nx - 1;
+    const bool out_held = at_out && k.hold_out != 0;
+    auto held = [&](const RowK& r) {
+        return (kExt && g.frame_t && on_frame(r)) || at_in || out_held;
+    };
+    auto trix = [&](auto v) {
+        if (!open_x) return tri(v);
+        auto m = at_xm(v), p = at_xp(v);
+        if (at_in) m = v;
+        if (at_out) p = v;
+        decltype(tri(v)) t;
+        t.c = v;
+        t.a = p + m;
+        t.d = p - m;
+        return t;
+    };
+    const bool ramp = kExt && k.wall_ramp != 0;
+    const PhysR<R>& kr = pr<R>(k);
+    const R T_ref = kr.T_ref, dTw = kr.dT_wall, rho_ref = kr.rho_ref;
+    const R dTw_x = ramp ? (R)(k.dT_wall + (k.dT_w_end - k.dT_wall) * (double)cx / (double)(g.Nx - 1))
+                         : (R)k.dT_wall;
+    const bool frame_rho = kExt && g.frame_rho != 0;
+    const bool props = kExt && (k.flags & kPhaseProps) != 0;
+    const bool eos_cs = kExt && (k.flags & kEosCS) != 0;
+    const bool freezeT = (k.flags & kFreezeT) != 0;
+    const bool single = (k.flags & kSinglePhase) != 0;
+    const bool top_mixed = kExt && (k.flags & kTopMixed) != 0;
+    const bool adiab = top_mixed && !(cx >= k.cold_x0 && cx < k.cold_x1);
+    const PhysR<R>& cv = kr;
+
+    const int ya = g.y_first + seg * g.seg_rows;
+    const int yb = min(ya + g.seg_rows, g.y_first + g.rows);
+    const int y0 = ya - kHalo + w * kRows;
+    const int wS = max(w - 1, 0), wN = min(w + 1, kWaves - 1);
+
+    const unsigned esz = (unsigned)sizeof(S);
+    const __amdgpu_buffer_rsrc_t rb = make_rsrc(B.base, B.span);
+    const unsigned vx = x * esz, vm = xm * esz, vp = xp * esz, vlo = x * 4u;
+    const unsigned rowb = (unsigned)g.pitch * esz, rowb_lo = (unsigned)g.pitch * 4u;
+    const unsigned P = g.plane * esz;
+
+    RowK rk[kRows];
+    S raw[kRows][9], rawT[kRows];
+    float rawlo[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        rk[r] = row_info(y0 + r, g);
+        if (y0 + r >= yb + kHalo) rk[r].fluid = false;
+        const RowK rS = rk[r].fluid ? rk[r] : row_info(g.y_first, g);
+        pull_row_buf<S>(rb, g, rS, B.fin, vx, vm, vp, raw[r]);
+        rawT[r] = bload(rb, vx, B.Tin + (unsigned)rS.sr * rowb, S(0));
+        rawlo[r] = kMX ? bload(rb, vlo, B.lo_in + (unsigned)rS.sr * rowb_lo, 0.0f) : 0.0f;
+    }
+    // ---- A: rho, j, psi -------------------------------------------------------
+    // the inlet density only where the tile holds the inlet column; the
+    // drive by the last wave alone, whose rows are mostly halo
+    const double rho_in = (open_x && __builtin_amdgcn_ballot_w64(at_in)) ? inlet_density(k, n) : 0.0;
+    if (w == kWaves - 1) L.drive = (R)drive_at(k, n);
+    R d[kRows][9], rho[kRows], drho[kRows], jx[kRows], jy[kRows], tn[kRows];
+    double psi[kRows], drd_[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const int y = y0 + r;
+        if (rk[r].fluid) {
+            R* dc = d[r];
+#pragma unroll
+            for (int q = 0; q < 9; ++q) dc[q] = (R)raw[r][q];
+            if (open_x) zou_he<R>(dc, at_in, at_out, rho_in, k, rk[r].bb_lo || rk[r].bb_hi);
+            double drd;
+            if (kMX) {
+                drd = (double)dc[0] + (double)(R)rawlo[r];
+#pragma unroll
+                for (int q = 1; q < 9; ++q) drd += (double)dc[q];
+            } else {
+                R s = ((dc[0] + dc[1]) + (dc[2] + dc[3])) +
+                      ((dc[4] + dc[5]) + (dc[6] + dc[7])) + dc[8];
+                drd = (double)s;
+            }
+            jx[r] = (dc[1] - dc[3]) + (dc[5] - dc[6]) + (dc[8] - dc[7]);
+            jy[r] = (dc[2] - dc[4]) + (dc[5] + dc[6]) - (dc[7] + dc[8]);
+            if (frame_rho && on_frame(rk[r])) {
+                drd = k.rho_frame - k.rho_ref;
+                jx[r] = jy[r] = 0;
+            }
+            drho[r] = (R)drd;
+            drd_[r] = drd;
+            const double rho_d = k.rho_ref + drd;
+            rho[r] = (R)rho_d;
+            tn[r] = (R)rawT[r];
+            const double Td = k.T_ref + (double)tn[r];
+            bool clamped;
+            psi[r] = psi_eos<sizeof(S) == 4, kExt>(rho_d, Td, k, clamped);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 9; ++q) d[r][q] = 0;
+            drho[r] = jx[r] = jy[r] = 0;
+            drd_[r] = 0.0;
+            rho[r] = rho_ref;
+            tn[r] = ramp ? dTw_x : ((top_mixed && y <= 0) ? (R)k.dT_w_bot : dTw);
+            psi[r] = k.psi_wall_eff;
+        }
+    }
+    L.psi[w][0][lane] = psi[0];
+    L.psi[w][1][lane] = psi[kRows - 1];
+    L.tn[w][0][lane] = tn[0];
+    L.tn[w][1][lane] = tn[kRows - 1];
+    __syncthreads();
+    // ---- B: forces, u, collision -----------------------------------------------
+    unsigned health = 0;
+    const R drive_r = L.drive;
+    R ux[kRows], uy[kRows], lam[kRows];
+    {
+        Tri<double> pS = trix(L.psi[wS][1][lane]), pC = trix(psi[0]), pN;
+        const double psi_up = L.psi[wN][0][lane];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const int y = y0 + r;
+            const RowK& rB = rk[r];
+            pN = trix(r + 1 < kRows ? psi[r + 1 < kRows ? r + 1 : r] : psi_up);
+            ux[r] = uy[r] = 0;
+            lam[r] = (R)k.lambda;
+            if (rB.fluid && y >= ya - 4 && y < yb + 4) {
+                double Fxd = 0.0, Fyd = 0.0, Fmx = 0.0, Fmy = 0.0;
+                if (!single) {
+                    pair_force(pS, pC, pN, k.negG, Fxd, Fyd);
+                    Fmx = Fxd;
+                    Fmy = Fyd - wall_adhesion_y(rB, pC.c, k);
+                } else {
+                    Fyd = wall_adhesion_y(rB, pC.c, k);
+                }
+                const R rh = rho[r];
+                R Fx = (R)Fxd + rh * drive_r + (rh - kr.rho_v) * kr.g_x;
+                R Fy = (R)Fyd + (rh - kr.rho_v) * kr.g_y;
+                const R rinv = rcp_r(rh);
+                R u = (jx[r] + (R)0.5 * Fx) * rinv;
+                R v = (jy[r] + (R)0.5 * Fy) * rinv;
+                const bool resB = frame_rho && on_frame(rB);
+                if (resB) u = v = 0;
+                ux[r] = u;
+                uy[r] = v;
+                if (props) {
+                    R fr = (rh - kr.rho_g) * kr.inv_drho;
+                    fr = fr < (R)0 ? (R)0 : (fr > (R)1 ? (R)1 : fr);
+                    lam[r] = (R)k.lambda + (R)(k.lam_l - k.lambda) * fr;
+                }
+                if (y >= ya && y < yb) {
+                    R th = 0;
+                    if (!single && pC.c > 0.0)
+                        th = (R)((Fmx * Fmx + Fmy * Fmy) * rcp_d<sizeof(S) == 4 ? 1 : 2>(pC.c * pC.c));
+                    R fr = (rh - kr.rho_g) * kr.inv_drho;
+                    fr = fr < (R)0 ? (R)0 : (fr > (R)1 ? (R)1 : fr);
+                    const R sv = rcp_r(kr.tau_g + fr * kr.dtau);
+                    R dn[9];
+#pragma unroll
+                    for (int q = 0; q < 9; ++q) dn[q] = d[r][q];
+                    collide<R>(dn, drho[r], rh, rinv, u, v, Fx, Fy, th, sv, cv);
+                    if (resB) {
+                        const double dr = k.rho_frame - k.rho_ref;
+#pragma unroll
+                        for (int q = 0; q < 9; ++q)
+                            dn[q] = (R)((q == 0 ? 4.0 / 9 : (q < 5 ? 1.0 / 9 : 1.0 / 36)) * dr);
+                    }
+                    if (store_lane) {
+                        health += pC.c == 0.0 ? 1u : 0u;
+                        if (!(__builtin_isfinite(rh) && __builtin_isfinite(tn[r])))
+                            health |= 0x80000000u;
+                        const unsigned so = B.fout + (unsigned)rB.sr * rowb;
+                        if (kMX) {
+                            double rest = drd_[r];
+#pragma unroll
+                            for (int q = 1; q < 9; ++q) rest -= (double)(S)dn[q];
+                            const float hi = (float)rest;
+                            bstore((S)hi, rb, vx, so);
+                            bstore((float)(rest - (double)hi), rb, vlo,
+                                   B.lo_out + (unsigned)rB.sr * rowb_lo);
+                        } else {
+                            bstore((S)dn[0], rb, vx, so);
+                        }
+#pragma unroll
+                        for (int q = 1; q < 9; ++q) bstore((S)dn[q], rb, vx, q * P + so);
+                    }
+                }
+            }
+            pS = pC;
+            pC = pN;
+        }
+    }
+    if (freezeT) {
+        flush_health(B.stat, health);
+        return;
+    }
+    L.ux[w][0][lane] = ux[0];
+    L.ux[w][1][lane] = ux[kRows - 1];
+    L.uy[w][0][lane] = uy[0];
+    L.uy[w][1][lane] = uy[kRows - 1];
+    if (kExt) {
+        L.lam[w][0][lane] = lam[0];
+        L.lam[w][1][lane] = lam[kRows - 1];
+    }
+    __syncthreads();
+    // the value row y + 1 shows a temperature stencil of row r (C: the row's own)
+    auto top = [&](const RowK& r, R N, R C) {
+        return (kExt && top_mixed && r.bb_hi) ? (adiab ? C : dTw) : N;
+    };
+    // ---- C: div u, coefficients, h1 -----------------------------------------------
+    R t[kRows], acc[kRows];
+    Coef<R> cf[kRows];
+    {
+        Tri<R> xS = trix(L.ux[wS][1][lane]), xC = trix(ux[0]), xN;
+        Tri<R> yS = trix(L.uy[wS][1][lane]), yC = trix(uy[0]), yN;
+        Tri<R> tS = trix(L.tn[wS][1][lane]), tC = trix(tn[0]), tN;
+        Tri<R> lS = tri_const<R>(0), lC = lS, lN = lS;
+        if (props) {
+            lS = trix(L.lam[kExt ? wS : 0][1][lane]);
+            lC = trix(lam[0]);
+        }
+        const R x_up = L.ux[wN][0][lane], y_up = L.uy[wN][0][lane], t_up = L.tn[wN][0][lane];
+        const R l_up = kExt ? L.lam[kExt ? wN : 0][0][lane] : (R)0;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const int y = y0 + r, rn = r + 1 < kRows ? r + 1 : r;
+            xN = trix(r + 1 < kRows ? ux[rn] : x_up);
+            yN = trix(r + 1 < kRows ? uy[rn] : y_up);
+            tN = trix(top(rk[r], r + 1 < kRows ? tn[rn] : t_up, tn[r]));
+            if (props) lN = trix(r + 1 < kRows ? lam[rn] : l_up);
+            t[r] = tn[r];
+            acc[r] = 0;
+            if (rk[r].fluid && y >= ya - 3 && y < yb + 3) {
+                const R dv = div_u<R>(xS, xC, xN, yS, yC, yN);
+                R lam_c = cv.lambda, glx = 0, gly = 0, inv_cv = cv.inv_Cv;
+                if (props) {
+                    const R third = (R)1 / 3, twelfth = (R)1 / 12;
+                    lam_c = lC.c;
+                    glx = lC.d * third + (lN.d + lS.d) * twelfth;
+                    gly = (lN.c - lS.c) * third + (lN.a - lS.a) * twelfth;
+                    R fr = (rho[r] - kr.rho_g) * kr.inv_drho;
+                    fr = fr < (R)0 ? (R)0 : (fr > (R)1 ? (R)1 : fr);
+                    inv_cv = rcp_r((R)(1.0 / k.inv_Cv) + (R)(k.cv_l - 1.0 / k.inv_Cv) * fr);
+                }
+                cf[r] = heat_coef<R>(rho[r], xC.c, yC.c, dv, T_ref + tC.c, T_ref, cv, eos_cs,
+                                     props, lam_c, glx, gly, inv_cv,
+                                     kExt ? (R)k.alpha_max : (R)0);
+                R h1 = heat_rhs<R>(tS, tC, tN, cf[r], T_ref);
+                if (held(rk[r])) h1 = 0;
+                acc[r] = h1;
+                t[r] = tn[r] + (R)0.5 * h1;
+            }
+            xS = xC; xC = xN; yS = yC; yC = yN; tS = tC; tC = tN;
+            lS = lC; lC = lN;
+        }
+    }
+    // ---- D, E: h2, h3 ------------------------------------------------------------
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        L.st[s][w][0][lane] = t[0];
+        L.st[s][w][1][lane] = t[kRows - 1];
+        __syncthreads();
+        const int reach = 2 - s;
+        Tri<R> tS = trix(L.st[s][wS][1][lane]), tC = trix(t[0]), tN;
+        const R t_up = L.st[s][wN][0][lane];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const int y = y0 + r, rn = r + 1 < kRows ? r + 1 : r;
+            const R tc = t[r];
+            tN = trix(top(rk[r], r + 1 < kRows ? t[rn] : t_up, tc));
+            if (rk[r].fluid && y >= ya - reach && y < yb + reach) {
+                R h = heat_rhs<R>(tS, tC, tN, cf[r], T_ref);
+                if (held(rk[r])) h = 0;
+                acc[r] += (R)2 * h;
+                t[r] = s == 0 ? tn[r] + (R)0.5 * h : tn[r] + h;
+            }
+            tS = tC;
+            tC = tN;
+        }
+    }
+    // ---- F: h4, T(n+1) -------------------------------------------------------------
+    L.st[2][w][0][lane] = t[0];
+    L.st[2][w][1][lane] = t[kRows - 1];
+    __syncthreads();
+    {
+        Tri<R> tS = trix(L.st[2][wS][1][lane]), tC = trix(t[0]), tN;
+        const R t_up = L.st[2][wN][0][lane];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const int y = y0 + r, rn = r + 1 < kRows ? r + 1 : r;
+            tN = trix(top(rk[r], r + 1 < kRows ? t[rn] : t_up, t[r]));
+            if (rk[r].fluid && y >= ya && y < yb) {
+                R h4 = heat_rhs<R>(tS, tC, tN, cf[r], T_ref);
+                if (held(rk[r])) h4 = 0;
+                const R tnew = tn[r] + (acc[r] + h4) * ((R)1 / 6);
+                if (own_lane) bstore((S)tnew, rb, vx, B.Tout + (unsigned)rk[r].sr * rowb);
+            }
+            tS = tC;
+            tC = tN;
+        }
+    }
+    flush_health(B.stat, health);
+}
+
+template <class S, bool kMX, bool kExt, int kRows, int kWaves>
+__global__ __launch_bounds__(kLanes* kWaves) __attribute__((amdgpu_waves_per_eu(4)))
+void tile_kernel(Grid g, Phys k, Bufs<S> B, long long n) {
+    __shared__ TileLds<typename RealOf<S>::T, kWaves, kExt> L;
+    const int unit = unit_of_block(gridDim.x);
+    if (unit >= g.n_units) return;  // whole workgroups only
+    tile_unit<S, kMX, kExt, kRows, kWaves>(g, k, B, n, unit, L);
+}
+
 // Step i of a chunk over a batch of channels.  The slot of a unit is found by
 // a binary search over the slots' first units (wave-uniform).
 template <bool kExt>
@@ -1548,10 +1922,34 @@ bool needs_ext(const Grid& g, const Phys& k) {
            (k.flags & (kEosCS | kPhaseProps | kTopMixed));
 }
 
+template <class S, bool kMX, bool kExt, int kTile>
+static hipError_t launch_tile(const Grid& g, const Phys& k, const Bufs<S>& b, int64_t n,
+                              hipStream_t s) {
+    constexpr TileShape t = kTiles[kTile];
+    hipLaunchKernelGGL((tile_kernel<S, kMX, kExt, t.rows, t.waves>), dim3(g.n_blocks_pad),
+                       dim3(kLanes * t.waves), 0, s, g, k, b, (long long)n);
+    return hipGetLastError();
+}
+template <class S, bool kMX, bool kExt>
+static hipError_t tile_impl(const Grid& g, const Phys& k, const Bufs<S>& b, int64_t n,
+                            hipStream_t s) {
+    if (g.tile == kTileFlat) return launch_tile<S, kMX, kExt, kTileFlat>(g, k, b, n, s);
+    if constexpr (sizeof(S) == 8) {
+        if (g.tile == kTileTall) return launch_tile<S, kMX, kExt, kTileTall>(g, k, b, n, s);
+    } else {
+        if (g.tile == kTileMid) return launch_tile<S, kMX, kExt, kTileMid>(g, k, b, n, s);
+        if (g.tile == kTileWide) return launch_tile<S, kMX, kExt, kTileWide>(g, k, b, n, s);
+    }
+    return hipErrorInvalidValue;
+}
+
 template <class S, bool kMX>
 static hipError_t step_impl(const Grid& g, const Phys& k, const Bufs<S>& b, int64_t n,
                             hipStream_t s) {
     if (g.n_units <= 0) return hipSuccess;
+    if (g.tile)
+        return needs_ext(g, k) ? tile_impl<S, kMX, true>(g, k, b, n, s)
+                               : tile_impl<S, kMX, false>(g, k, b, n, s);
     if (needs_ext(g, k))
         hipLaunchKernelGGL((step_kernel<S, kMX, true>), dim3(g.n_blocks_pad),
                            dim3(kLanes * kWavesPerBlock), 0, s, g, k, b, (long long)n);
@@ -1569,6 +1967,9 @@ hipError_t launch_step_f32(const Grid& g, const Phys& k, const Bufs<float>& b, b
 hipError_t launch_step_f64(const Grid& g, const Phys& k, const Bufs<double>& b, int64_t n,
                            hipStream_t s) {
     if (g.n_units <= 0) return hipSuccess;
+    if (g.tile)
+        return needs_ext(g, k) ? tile_impl<double, false, true>(g, k, b, n, s)
+                               : tile_impl<double, false, false>(g, k, b, n, s);
     if (needs_ext(g, k))
         hipLaunchKernelGGL(step_kernel_f64<true>, dim3(g.n_blocks_pad),
                            dim3(kLanes * kWavesPerBlock), 0, s, g, k, b, (long long)n);

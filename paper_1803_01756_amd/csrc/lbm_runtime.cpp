@@ -397,7 +397,32 @@ int default_seg_rows(const lbm_params& p, int rows, int min_rows) {
     return std::min(sr, rows);
 }
 
-void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, Grid& g) {
+int default_tile(const lbm_params& p, int rows) {
+    const int strips = (p.Nx + lbmk::kOwned - 1) / lbmk::kOwned;
+    const auto units = [&](int t) {
+        const int own = lbmk::kTiles[t].own();
+        return (long long)strips * ((rows + own - 1) / own);
+    };
+    // While a grid is a few workgroups per CU, the time of a step is one
+    // workgroup's way through the stages, and the flattest tile (one row per
+    // wave) is the shortest: 128 x 32 in 5.8 us against 17.8 marching,
+    // 1024 x 128 (399 tiles) in 8.9 against 21.5.  Beyond that its 10 halo
+    // rows per 6 of its own fill the chip (2048 x 256: 22.1 us) and taller
+    // tiles take over (17.6 and 16.9 us, 31.0 marching).  Past two rounds of
+    // those (two workgroups per CU) the march's fewer halo rows win: 4096 x
+    // 512 in 48.9 us against 50.9, 8192 x 512 in 93.1 against 107.8; at
+    // 2048 x 512 (912 tiles) it is 37.5 against 28.3.
+    if (p.precision == LBM_FP64) {
+        // FP64: one workgroup per CU (its halo exchange fills the LDS)
+        if (units(lbmk::kTileFlat) <= 256) return lbmk::kTileFlat;
+        return units(lbmk::kTileTall) <= 1024 ? lbmk::kTileTall : lbmk::kTileNone;
+    }
+    if (units(lbmk::kTileFlat) <= 512) return lbmk::kTileFlat;
+    if (units(lbmk::kTileMid) <= 512) return lbmk::kTileMid;
+    return units(lbmk::kTileWide) <= 1024 ? lbmk::kTileWide : lbmk::kTileNone;
+}
+
+void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, Grid& g, int tile) {
     g.Nx = p.Nx;
     g.Ny = p.Ny;
     g.pitch = L.pitch;
@@ -409,10 +434,14 @@ void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, Grid& g) {
     g.y_first = g.periodic_y ? 0 : 1;
     g.plane = (unsigned)L.plane;
     g.n_strips = (p.Nx + lbmk::kOwned - 1) / lbmk::kOwned;
+    g.tile = tile;
+    if (tile != lbmk::kTileNone) seg_rows = lbmk::kTiles[tile].own();
     g.seg_rows = std::max(1, std::min(seg_rows, g.rows));
     g.n_segs = (g.rows + g.seg_rows - 1) / g.seg_rows;
     g.n_units = g.n_strips * g.n_segs;
-    const int nb = (g.n_units + lbmk::kWavesPerBlock - 1) / lbmk::kWavesPerBlock;
+    const int nb = tile != lbmk::kTileNone
+                       ? g.n_units
+                       : (g.n_units + lbmk::kWavesPerBlock - 1) / lbmk::kWavesPerBlock;
     g.n_blocks_pad = (nb + 7) / 8 * 8;
 }
 
@@ -513,9 +542,12 @@ namespace {
 
 using lbmhost::default_seg_rows;
 
-void set_grid(lbm_sim* s, int seg_rows) {
-    lbmhost::fill_grid(s->p, s->L, seg_rows, s->g);
+void set_grid(lbm_sim* s, int seg_rows, int tile = lbmk::kTileNone) {
+    lbmhost::fill_grid(s->p, s->L, seg_rows, s->g, tile);
     s->seg_rows = s->g.seg_rows;
+}
+void set_default_grid(lbm_sim* s) {
+    set_grid(s, default_seg_rows(s->p, s->L.rows), lbmhost::default_tile(s->p, s->L.rows));
 }
 
 void set_phys(lbm_sim* s) { lbmhost::fill_phys(s->p, s->k); }
@@ -774,7 +806,7 @@ lbm_status lbm_create(const lbm_params* pin, const double* rho0, void* workspace
         s->owns_stream = true;
     }
     set_phys(s);
-    set_grid(s, default_seg_rows(p, s->L.rows));
+    set_default_grid(s);
     // zero everything (pitch padding stays zero), upload rho0, start state
     e = hipMemsetAsync(s->base, 0, s->L.total, s->stream);
     if (e == hipSuccess)
@@ -948,17 +980,18 @@ lbm_status lbm_load(lbm_sim* s, const void* host, size_t bytes) {
     HIPCHK(hipMemsetAsync(s->stat(), 0, lbmhost::kStatWords * sizeof(unsigned long long),
                           s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
-    const int seg = s->seg_rows;
+    const int seg = s->seg_rows, tile = s->g.tile;
     s->p = h.p;
     s->n = h.n;
     set_phys(s);
-    set_grid(s, seg);
+    set_grid(s, seg, tile);
     return LBM_OK;
 }
 
 lbm_status lbm_set_launch(lbm_sim* s, int32_t seg_rows) {
     if (!s) return fail(LBM_EINVAL, "null sim");
-    set_grid(s, seg_rows > 0 ? seg_rows : default_seg_rows(s->p, s->L.rows));
+    if (seg_rows > 0) set_grid(s, seg_rows);
+    else set_default_grid(s);
     return LBM_OK;
 }
 
@@ -1017,13 +1050,22 @@ lbm_status lbm_autotune(lbm_sim* s, int32_t steps_per_trial, double* best_ms) {
     cands.push_back(default_seg_rows(s->p, s->L.rows));
     std::sort(cands.begin(), cands.end());
     cands.erase(std::unique(cands.begin(), cands.end()), cands.end());
+    // the tile shapes, as the negative of their index
+    for (int t = 1; t < lbmk::kTileCount; ++t)
+        if ((t == lbmk::kTileTall) ? s->p.precision == LBM_FP64
+                                   : (t == lbmk::kTileFlat || s->p.precision != LBM_FP64))
+            cands.push_back(-t);
+    const auto take = [&](int c) {
+        if (c > 0) set_grid(s, c);
+        else set_grid(s, 0, -c);
+    };
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (e == hipSuccess) e = hipEventCreate(&ev0);
     if (e == hipSuccess) e = hipEventCreate(&ev1);
     double best = 1e300;
-    int best_seg = s->seg_rows;
+    int best_seg = s->g.tile ? -s->g.tile : s->seg_rows;
     for (size_t ci = 0; ci < cands.size() && e == hipSuccess; ++ci) {
-        set_grid(s, cands[ci]);
+        take(cands[ci]);
         for (int w = 0; w < 2 && e == hipSuccess; ++w) e = enqueue_step(s);
         if (e == hipSuccess) e = hipEventRecord(ev0, s->stream);
         for (int i = 0; i < steps_per_trial && e == hipSuccess; ++i) e = enqueue_step(s);
@@ -1043,7 +1085,7 @@ lbm_status lbm_autotune(lbm_sim* s, int32_t steps_per_trial, double* best_ms) {
     if (ev0) (void)hipEventDestroy(ev0);
     if (ev1) (void)hipEventDestroy(ev1);
     (void)hipFree(snap);
-    set_grid(s, best_seg);
+    take(best_seg);
     if (e != hipSuccess) return fail(LBM_EDEVICE, "autotune: %s", hipGetErrorString(e));
     if (best_ms) *best_ms = best;
     return LBM_OK;

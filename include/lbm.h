@@ -303,17 +303,14 @@ size_t lbm_state_bytes(const lbm_sim* sim);
 lbm_status lbm_save(lbm_sim* sim, void* host, size_t bytes);
 lbm_status lbm_load(lbm_sim* sim, const void* host, size_t bytes);
 
-/* Launch shape of the fused step kernel: each wave owns a strip of 54
- * columns and marches over seg_rows fluid rows.  seg_rows <= 0 restores the
- * default: a small or middling grid (up to two rounds of workgroups) takes
- * tiles of 54 columns x 6 to 22 rows, one workgroup each; a larger one
- * segments sized for about 3072 waves (one resident round at three
- * waves per SIMD on 256 CUs; 2048 and two waves for FP64 and mass-exact
- * storage), at least 2 rows, with seg_rows + 10 a multiple of 6 (pool slots:
- * at least 14 rows, see lbm_pool_set_launch).  lbm_autotune times candidate
- * shapes of both kinds instead.  lbm_get_launch reports the rows of a
- * segment or tile and how many of them the step launches.  The result of a
- * step does not depend on the shape (bitwise). */
+/* Launch shape of the fused step kernel: the grid is cut into strips of 54
+ * columns and segments of seg_rows fluid rows; a workgroup takes a segment, or
+ * an even share of one taller than the tallest tile (26 rows).  seg_rows <= 0
+ * restores the default: tiles of up to 6 rows on a small grid (a few per CU),
+ * 14 on a middling and 26 on a large one (FP64: 6, 22 and 26).  lbm_autotune
+ * times candidate shapes instead.  lbm_get_launch reports seg_rows and the
+ * number of segments.  The result of a step does not depend on the shape
+ * (bitwise). */
 lbm_status lbm_set_launch(lbm_sim* sim, int32_t seg_rows);
 lbm_status lbm_get_launch(const lbm_sim* sim, int32_t* seg_rows, int32_t* waves);
 
@@ -394,15 +391,15 @@ lbm_status lbm_pool_info(const lbm_pool* pool, int32_t* active, size_t* bytes_us
 /* Time level of a slot (after the work enqueued so far), -1 if no such slot. */
 int64_t lbm_pool_slot_time(const lbm_pool* pool, int32_t slot);
 
-/* Rows per wave of every slot's launch shape, capped at the slot's rows
- * (<= 0: the per-slot default, segments of at least 14 rows sized toward
- * one resident round of waves; this also drops a tuned policy). */
+/* Rows of a segment of every slot's launch shape, capped at the slot's rows
+ * (<= 0: the default, segments of up to 14 rows, or up to 26 in a large
+ * batch; this also drops a tuned policy). */
 lbm_status lbm_pool_set_launch(lbm_pool* pool, int32_t seg_rows);
 
 /* Time launch policies on the slots that have steps left (all admitted slots
  * if none has) and keep the fastest for them and for later admissions.  A
  * policy gives each bucket of fluid rows (up to 32, 64, 128, 256, more) a
- * target segment height, from 8 rows to whole slots; each slot then uses
+ * target segment height, from 8 to 26 rows; each slot then uses
  * segments of about that height, balanced over its rows.  The search times
  * the default heuristic, one target for all buckets, then each bucket
  * present in turn with the others fixed, steps_per_trial batched steps per
@@ -415,7 +412,7 @@ lbm_status lbm_pool_set_launch(lbm_pool* pool, int32_t seg_rows);
  * the steps do not depend on the policy (bitwise). */
 lbm_status lbm_pool_autotune(lbm_pool* pool, int32_t steps_per_trial, double* best_ms);
 
-/* Launch shape of a slot: rows per wave and waves per step. */
+/* Launch shape of a slot: rows of a segment and segments of a step. */
 lbm_status lbm_pool_slot_launch(const lbm_pool* pool, int32_t slot, int32_t* seg_rows,
                                 int32_t* waves);
 

@@ -42,13 +42,17 @@ lbm_status validate(const lbm_params& p);
 // every fluid node needs 0 < b rho below the packing limit and a positive
 // Eq. 10 argument 2 (P_EOS - rho/3) / G at its initial temperature.
 lbm_status check_initial(const lbm_params& p, const double* rho0);
-int default_seg_rows(const lbm_params& p, int rows, int min_rows = 2);
-// The tile shape a channel stepped alone takes by default (kTileNone: the
-// march, with default_seg_rows).
+// Tall tiles from which on they are the default (default_tile).
+constexpr long long kTallTiles = 2048;
+// The tile shape of a channel stepped alone by default, and the smallest one
+// that holds seg_rows rows (the tallest if none does).
 int default_tile(const lbm_params& p, int rows);
-// Grid of a launch shape; a tile shape brings its own seg_rows.
-void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, lbmk::Grid& g,
-               int tile = lbmk::kTileNone);
+int tile_for(const lbm_params& p, int seg_rows);
+// Grid of a launch with segments of seg_rows rows in tiles of shape `tile`:
+// segments taller than a tile are split evenly.
+void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, int tile, lbmk::Grid& g);
+// Segments of about `target` rows, balanced over the channel's rows.
+int balanced_rows(int rows, int target);
 void fill_phys(const lbm_params& p, lbmk::Phys& k);
 
 }  // namespace lbmhost

@@ -16,22 +16,31 @@ constexpr int kLanes = 64;
 constexpr int kHalo = 5;
 constexpr int kOwned = kLanes - 2 * kHalo;
 
-// Launch shapes of the step.  kTileNone: every wave marches over a segment of
-// seg_rows rows.  The others: a workgroup of `waves` waves with `rows` rows
-// each holds a tile of up to rows x waves - 2 kHalo rows and its halo.
+// Tiles of the step: a workgroup of `waves` waves with `rows` rows each holds
+// up to own() rows of a strip and their halo; per_simd is the number of waves
+// per SIMD its register budget is held to.  The waves of a workgroup are a
+// multiple of four, one share for each SIMD: with 9 or 10 a second workgroup
+// does not fit beside the first (8192 x 512: 118 and 112 us for 96 with 8).
+// FP32: Mid keeps three workgroups on a CU, Tall two; taller waves of five
+// rows (5 x 8) leave four waves per SIMD and measured 87.3 against Tall's 84.3.
+// FP64: the halo exchange in LDS leaves one workgroup per CU.
 struct TileShape {
-    int rows, waves;
+    int rows, waves, per_simd;
     constexpr int own() const { return rows * waves - 2 * kHalo; }
 };
-enum { kTileNone = 0, kTileFlat, kTileMid, kTileWide, kTileTall, kTileCount };
-constexpr TileShape kTiles[kTileCount] = {{0, 0}, {1, 16}, {3, 8}, {4, 8}, {2, 16}};
+enum { kTileFlat, kTileMid, kTileTall, kTileFlat64, kTileMid64, kTileTall64, kTileCount };
+constexpr TileShape kTiles[kTileCount] = {{1, 16, 4}, {3, 8, 6},  {3, 12, 6},   // FP32
+                                          {1, 16, 4}, {2, 16, 4}, {3, 12, 3}};  // FP64
 
 // Constants that enter arithmetic done in the storage precision R, given in
 // R on the host so that the kernels never convert them per use.
 template <class R>
 struct PhysR {
-    R s_rho, s_e, s_z, s_j, s_q, c_e, c_z;
-    R b, rkA, rkB1, rkB2, inv_Cv, lambda;
+    // the collision's combinations of the Eq. 3 rates (collide())
+    R se4, se12, se36;  // (1 - s_e)/4, s_e/12, s_e/36
+    R q_u, q_F, q_th;   // the factors of rho u^2, u.F and |F_m|^2 / psi^2 in Q
+    R xc, xd;           // s_q/12, (3 - 2 s_q)/12
+    R b, rkA, rkB1, rkB2, inv_Cv, lam6;  // lam6 = lambda / 6
     R T_ref, dT_wall, rho_ref, rho_v, g_x, g_y;
     R rho_g, inv_drho, tau_g, dtau;
 };
@@ -41,11 +50,9 @@ struct PhysR {
 struct Phys {
     double rho_ref, T_ref, dT_wall;     // storage references; T_w - T_ref
     double a, b, R, kappa, inv_Tc;      // Eq. 11
-    double inv_G, negG;                 // Eq. 10 (1/G) and Eq. 9 (-G)
+    double two_inv_G, negG12;           // Eq. 10 (2/G) and Eq. 9 (-G/12)
     double psi_wall_eff;                // psi_w G_w / G: solid-row potential
     double Gw_psiw;                     // G_w psi_w (Eq. 14 on the wall rows)
-    double c_e, c_z;                    // 12 theta / (tau_e - 1/2), same for zeta
-    double s_rho, s_e, s_z, s_j, s_q;   // Eq. 3 rates
     double tau_g, dtau, rho_g, inv_drho;// Eq. 5 (inv_drho = 0: constant tau)
     double inv_Cv, lambda;              // Eq. 16
     double g_osc, period;               // drive g_osc sin(2 pi n / period) along +x
@@ -79,8 +86,11 @@ struct Grid {
     int frame_t;       // T held at T_w on the frame: outermost columns (and rows if periodic_y)
     int frame_rho;     // the frame is a reservoir at rest with density rho_frame
     int open_x;        // Zou-He pressure inlet at x = 0, outlet at x = Nx-1
-    int tile;          // launch shape (kTile...)
-    int n_strips, n_segs, seg_rows, n_units, n_blocks_pad;
+    int tile;              // tile shape (kTile...)
+    int seg_rows;          // rows of a tile
+    int n_strips, n_segs;  // tiles across and up
+    int strips_per_xcd;    // > 0: strips of an XCD's chunk (tile_of_block)
+    int n_blocks;          // workgroups of a step, a multiple of 8
     unsigned plane;    // rows * pitch
 };
 
@@ -98,8 +108,6 @@ struct Bufs {
     // whose Eq. 10 argument was clamped (psi = 0)
     unsigned long long* stat;
 };
-
-constexpr int kWavesPerBlock = 4;
 
 // One fused time step n -> n+1 (pull-stream + bounce-back, psi, forces, u,
 // MRT collision, RK4 temperature) over all units of the grid.
@@ -122,17 +130,17 @@ struct Slot {
     int64_t n0;
     int cur_f, cur_T;
     int steps_left;
-    int unit_begin;  // first unit of this slot in the batch numbering
+    int block_begin;  // first workgroup of this slot in the batch
     unsigned long long* stat;  // the slot's health counters (see Bufs::stat)
 };
 
 // Step i of a chunk over every slot of the table (slots sorted by
-// unit_begin, total_units = sum of their units).
+// block_begin, total_blocks = sum of their workgroups), all with one tile shape.
 // ext: some slot uses an optional feature (frames, Carnahan-Starling EOS,
 // open ends, plate temperature ramp, phase-dependent properties, Sec. 3.2
 // plates), so the batch runs the kernel build that has them
-hipError_t launch_step_batched(const Slot* slots, int n_slots, int total_units, int step_i, bool ext,
-                               hipStream_t s);
+hipError_t launch_step_batched(const Slot* slots, int n_slots, int total_blocks, int tile,
+                               int step_i, bool ext, hipStream_t s);
 
 // rho, u (half force) and T at the current time level into device arrays of
 // Nx*Ny doubles; work holds 3*Nx*Ny doubles; *n_bad is incremented for

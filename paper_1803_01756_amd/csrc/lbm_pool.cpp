@@ -43,6 +43,7 @@ struct SlotState {
     int cur_f = 0, cur_T = 0;
     int64_t n = 0;           // time level after the work enqueued so far
     int64_t steps_left = 0;  // steps still to enqueue
+    int seg_rows = 0;        // rows of a segment of its launch shape
     bool ready_waited = false;
     bool reported = false;
     bool failed = false;     // retired early: its state became non-finite
@@ -68,10 +69,9 @@ int row_bucket(int rows) {
 }
 
 // Segments of about `target` rows, balanced over the slot's rows, with
-// seg + 10 (the recomputed halo rows) a multiple of the six-row unroll.
+// seg + 10 (the halo rows) a multiple of 6, as the targets have it.
 int balanced_seg_rows(int rows, int target) {
-    const int segs = std::max(1, (rows + target - 1) / target);
-    int sr = (rows + segs - 1) / segs;
+    int sr = lbmhost::balanced_rows(rows, target);
     sr = sr + (6 - (sr + 10) % 6) % 6;
     return std::min(sr, rows);
 }
@@ -92,6 +92,8 @@ struct lbm_pool {
     // tuned segment heights per bucket of fluid rows (lbm_pool_autotune;
     // 0: the default heuristic)
     int seg_target[kRowBuckets] = {};
+    // default segment height of the current batch (default_target)
+    int default_target = lbmk::kTiles[lbmk::kTileMid].own();
     // table of the batched kernel: device copy and two pinned host stagings
     lbmk::Slot* table_dev = nullptr;
     lbmk::Slot* table_host[2] = {nullptr, nullptr};
@@ -181,14 +183,27 @@ SlotState* get_slot(lbm_pool* P, int32_t id) {
     return &P->slots[id];
 }
 
+// Default segment height of a batch of slots: the line between the Mid and
+// the Tall tile lies where it does for a channel alone (default_tile).
+int default_target(const lbm_pool* P, const std::vector<int>& slots) {
+    const int tall = lbmk::kTiles[lbmk::kTileTall].own();
+    long long tiles = 0;
+    for (int id : slots)
+        tiles += (long long)P->slots[id].g.n_strips * ((P->slots[id].L.rows + tall - 1) / tall);
+    return tiles > lbmhost::kTallTiles ? tall : lbmk::kTiles[lbmk::kTileMid].own();
+}
+
+// The slot's segment height: the caller's, the tuned one, or the batch's
+// default.
 int seg_rows_for(const lbm_pool* P, const SlotState& s) {
     if (P->seg_cap > 0) return std::min(P->seg_cap, s.L.rows);
     const int t = P->seg_target[row_bucket(s.L.rows)];
     if (t > 0) return balanced_seg_rows(s.L.rows, t);
-    // many channels share one launch, so each keeps segments of at least
-    // 14 rows rather than aiming at a full round of waves by itself
-    return lbmhost::default_seg_rows(s.p, s.L.rows, 14);
+    return balanced_seg_rows(s.L.rows, P->default_target);
 }
+
+// The batch takes one tile shape: the smallest that holds every segment.
+int batch_tile(const lbm_params& p, int tallest) { return lbmhost::tile_for(p, tallest); }
 
 }  // namespace
 
@@ -305,7 +320,8 @@ lbm_status lbm_pool_admit(lbm_pool* P, const lbm_params* pin, const double* rho0
         o += lbmhost::align_up(L.plane * 4);
     }
     lbmhost::fill_phys(p, s.k);
-    lbmhost::fill_grid(p, L, seg_rows_for(P, s), s.g);
+    s.seg_rows = seg_rows_for(P, s);
+    lbmhost::fill_grid(p, L, s.seg_rows, lbmhost::tile_for(p, s.seg_rows), s.g);
     s.steps_left = nsteps;
     s.used = true;
     P->used += need;
@@ -363,7 +379,13 @@ lbm_status lbm_pool_run(lbm_pool* P, int32_t chunk) {
     P->table_next ^= 1;
     PCHK(hipEventSynchronize(P->table_free[b]));  // the staging copy from two chunks ago
     lbmk::Slot* tab = P->table_host[b];
-    int units = 0, longest = 0;
+    int blocks = 0, longest = 0, tallest = 1;
+    P->default_target = default_target(P, act);
+    for (int id : act) {
+        P->slots[id].seg_rows = seg_rows_for(P, P->slots[id]);
+        tallest = std::max(tallest, P->slots[id].seg_rows);
+    }
+    const int tile = batch_tile(P->slots[act[0]].p, tallest);
     bool ext = false;  // some slot needs the build with the optional features
     for (size_t j = 0; j < act.size(); ++j) {
         SlotState& s = P->slots[act[j]];
@@ -376,7 +398,7 @@ lbm_status lbm_pool_run(lbm_pool* P, int32_t chunk) {
         }
         const int take = (int)std::min<int64_t>(chunk, s.steps_left);
         lbmk::Slot& t = tab[j];
-        t.g = s.g;
+        lbmhost::fill_grid(s.p, s.L, s.seg_rows, tile, t.g);
         t.k = s.k;
         t.mem = s.mem;
         for (int q = 0; q < 2; ++q) {
@@ -388,16 +410,17 @@ lbm_status lbm_pool_run(lbm_pool* P, int32_t chunk) {
         t.cur_f = s.cur_f;
         t.cur_T = s.cur_T;
         t.steps_left = take;
-        t.unit_begin = units;
+        t.block_begin = blocks;
         t.stat = P->stat_dev + (size_t)act[j] * kSlotStat;
-        units += s.g.n_units;
+        blocks += t.g.n_blocks;
         longest = std::max(longest, take);
     }
     PCHK(hipMemcpyAsync(P->table_dev, tab, act.size() * sizeof(lbmk::Slot), hipMemcpyHostToDevice,
                         P->main));
     PCHK(hipEventRecord(P->table_free[b], P->main));
     for (int i = 0; i < longest; ++i)
-        PCHK(lbmk::launch_step_batched(P->table_dev, (int)act.size(), units, i, ext, P->main));
+        PCHK(lbmk::launch_step_batched(P->table_dev, (int)act.size(), blocks, tile, i, ext,
+                                       P->main));
     for (size_t j = 0; j < act.size(); ++j) {
         SlotState& s = P->slots[act[j]];
         const int take = (int)std::min<int64_t>(chunk, s.steps_left);
@@ -575,7 +598,7 @@ lbm_status lbm_pool_set_launch(lbm_pool* P, int32_t seg_rows) {
     if (seg_rows <= 0)
         for (int& t : P->seg_target) t = 0;
     for (SlotState& s : P->slots)
-        if (s.used) lbmhost::fill_grid(s.p, s.L, seg_rows_for(P, s), s.g);
+        if (s.used) s.seg_rows = seg_rows_for(P, s);
     return LBM_OK;
 }
 
@@ -583,8 +606,8 @@ lbm_status lbm_pool_slot_launch(const lbm_pool* P, int32_t id, int32_t* seg_rows
                                 int32_t* waves) {
     const SlotState* s = get_slot(const_cast<lbm_pool*>(P), id);
     if (!s) return fail(LBM_EINVAL, "no slot %d", id);
-    if (seg_rows) *seg_rows = s->g.seg_rows;
-    if (waves) *waves = s->g.n_units;
+    if (seg_rows) *seg_rows = s->seg_rows;
+    if (waves) *waves = s->g.n_strips * ((s->L.rows + s->seg_rows - 1) / s->seg_rows);
     return LBM_OK;
 }
 
@@ -637,19 +660,22 @@ lbm_status lbm_pool_autotune(lbm_pool* P, int32_t steps_per_trial, double* best_
               s.p.T_w_end > 0.0 || s.p.alpha_max > 0.0;
         present[row_bucket(s.L.rows)] = 1;
     }
+    const int dflt = default_target(P, act);
     // time one policy (segment-height target per bucket) over the copies
     int trial_steps = steps_per_trial;
     auto trial = [&](const int* target, double* ms_out) -> hipError_t {
-        int units = 0;
+        int blocks = 0, tallest = 1;
+        const auto height = [&](const SlotState& s) {
+            const int t = target[row_bucket(s.L.rows)];
+            return balanced_seg_rows(s.L.rows, t > 0 ? t : dflt);
+        };
+        for (int id : act) tallest = std::max(tallest, height(P->slots[id]));
+        const int tile = batch_tile(P->slots[act[0]].p, tallest);
         for (size_t j = 0; j < act.size(); ++j) {
             const SlotState& s = P->slots[act[j]];
-            const int t = target[row_bucket(s.L.rows)];
             lbmk::Slot& q = tab[j];
             q.k = s.k;
-            lbmhost::fill_grid(s.p, s.L,
-                               t > 0 ? balanced_seg_rows(s.L.rows, t)
-                                     : lbmhost::default_seg_rows(s.p, s.L.rows, 14),
-                               q.g);
+            lbmhost::fill_grid(s.p, s.L, height(s), tile, q.g);
             q.mem = shadow + at[j];
             for (int c = 0; c < 2; ++c) {
                 q.off_f[c] = (unsigned)(reinterpret_cast<char*>(s.f[c]) - s.mem);
@@ -660,18 +686,18 @@ lbm_status lbm_pool_autotune(lbm_pool* P, int32_t steps_per_trial, double* best_
             q.cur_f = s.cur_f;
             q.cur_T = s.cur_T;
             q.steps_left = trial_steps + 2;
-            q.unit_begin = units;
+            q.block_begin = blocks;
             q.stat = reinterpret_cast<unsigned long long*>(shadow + stat_at) + j * kSlotStat;
-            units += q.g.n_units;
+            blocks += q.g.n_blocks;
         }
         auto* dtab = reinterpret_cast<lbmk::Slot*>(shadow + tab_at);
         hipError_t r = hipMemcpyAsync(dtab, tab.data(), tab.size() * sizeof(lbmk::Slot),
                                       hipMemcpyHostToDevice, P->main);
         for (int i = 0; i < 2 && r == hipSuccess; ++i)
-            r = lbmk::launch_step_batched(dtab, (int)act.size(), units, i, ext, P->main);
+            r = lbmk::launch_step_batched(dtab, (int)act.size(), blocks, tile, i, ext, P->main);
         if (r == hipSuccess) r = hipEventRecord(ev0, P->main);
         for (int i = 0; i < trial_steps && r == hipSuccess; ++i)
-            r = lbmk::launch_step_batched(dtab, (int)act.size(), units, 2 + i, ext, P->main);
+            r = lbmk::launch_step_batched(dtab, (int)act.size(), blocks, tile, 2 + i, ext, P->main);
         if (r == hipSuccess) r = hipEventRecord(ev1, P->main);
         if (r == hipSuccess) r = hipEventSynchronize(ev1);
         float ms = 0.0f;
@@ -679,10 +705,9 @@ lbm_status lbm_pool_autotune(lbm_pool* P, int32_t steps_per_trial, double* best_
         *ms_out = ms / trial_steps;
         return r;
     };
-    // Segment heights with seg + 10 a multiple of 6, from the default
-    // heuristic's 14 rows up to whole slots.  First one height for every
+    // Segment heights up to the tallest tile.  First one height for every
     // bucket, then each bucket present in turn with the others fixed.
-    const int cands[] = {8, 14, 20, 26, 32, 38, 44, 56, 68, 80, 104, 128, 182, 254, 1 << 20};
+    const int cands[] = {8, 14, 20, 26};
     int cur[kRowBuckets] = {};
     double best = 1e300;
     if (e == hipSuccess) e = trial(cur, &best);  // the default heuristic
@@ -740,7 +765,7 @@ lbm_status lbm_pool_autotune(lbm_pool* P, int32_t steps_per_trial, double* best_
     P->seg_cap = 0;
     std::copy(cur, cur + kRowBuckets, P->seg_target);
     for (SlotState& s : P->slots)
-        if (s.used) lbmhost::fill_grid(s.p, s.L, seg_rows_for(P, s), s.g);
+        if (s.used) s.seg_rows = seg_rows_for(P, s);
     if (best_ms) *best_ms = best;
     return LBM_OK;
 }

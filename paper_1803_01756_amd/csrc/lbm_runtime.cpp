@@ -359,7 +359,8 @@ struct lbm_sim {
     bool owns_stream = false;
     int64_t n = 0;
     int fcur = 0, tcur = 0;
-    int seg_rows = 0;
+    int seg_rows = 0;  // rows of a segment (a tile or several)
+    int seg_arg = 0;   // the height asked for, 0: default
 
     template <class S>
     S* f(int b) const { return reinterpret_cast<S*>(base + L.off_f[b]); }
@@ -382,47 +383,43 @@ struct lbm_sim {
 
 namespace lbmhost {
 
-// default launch shape: enough waves to give each of the 1024 SIMDs about two
-// (the register budget of the fused kernel allows two resident per SIMD), but
-// segments of at least 16 rows so the 10 recomputed halo rows stay a minority.
-int default_seg_rows(const lbm_params& p, int rows, int min_rows) {
-    const int strips = (p.Nx + lbmk::kOwned - 1) / lbmk::kOwned;
-    // one resident round: 256 CUs x 4 SIMDs x 3 waves for the FP32 deviation
-    // build, 2 waves for the FP64 and mass-exact builds
-    const int want_units = p.precision == LBM_FP32_DEV ? 3072 : 2048;
-    int segs = std::max(1, (want_units + strips - 1) / strips);
-    int sr = (rows + segs - 1) / segs;
-    sr = std::max(sr, min_rows);
-    sr = sr + (6 - (sr + 10) % 6) % 6;  // seg + 10 a multiple of the 6-row unroll
-    return std::min(sr, rows);
+int balanced_rows(int rows, int target) {
+    const int segs = std::max(1, (rows + target - 1) / target);
+    return (rows + segs - 1) / segs;
 }
 
+static int strips_of(const lbm_params& p) { return (p.Nx + lbmk::kOwned - 1) / lbmk::kOwned; }
+
 int default_tile(const lbm_params& p, int rows) {
-    const int strips = (p.Nx + lbmk::kOwned - 1) / lbmk::kOwned;
-    const auto units = [&](int t) {
+    const auto tiles = [&](int t) {
         const int own = lbmk::kTiles[t].own();
-        return (long long)strips * ((rows + own - 1) / own);
+        return (long long)strips_of(p) * ((rows + own - 1) / own);
     };
     // While a grid is a few workgroups per CU, the time of a step is one
     // workgroup's way through the stages, and the flattest tile (one row per
-    // wave) is the shortest: 128 x 32 in 5.8 us against 17.8 marching,
-    // 1024 x 128 (399 tiles) in 8.9 against 21.5.  Beyond that its 10 halo
-    // rows per 6 of its own fill the chip (2048 x 256: 22.1 us) and taller
-    // tiles take over (17.6 and 16.9 us, 31.0 marching).  Past two rounds of
-    // those (two workgroups per CU) the march's fewer halo rows win: 4096 x
-    // 512 in 48.9 us against 50.9, 8192 x 512 in 93.1 against 107.8; at
-    // 2048 x 512 (912 tiles) it is 37.5 against 28.3.
+    // wave) is the shortest: 128 x 32 in 5.9 us against 7.4 (Mid) and 8.6
+    // (Tall), 1024 x 128 (399 flat tiles) 8.4 / 8.5 / 9.8.  Beyond that its 10
+    // halo rows per 6 of its own fill the chip (2048 x 256: 20.7 / 14.1 /
+    // 15.2).  From some four rounds of Tall tiles (two per CU) on, their fewer
+    // halo rows win over Mid's three resident workgroups: 4096 x 512 in 39.2
+    // (Mid) against 40.3, 8192 x 512 in 87.5 against 84.3.
     if (p.precision == LBM_FP64) {
-        // FP64: one workgroup per CU (its halo exchange fills the LDS)
-        if (units(lbmk::kTileFlat) <= 256) return lbmk::kTileFlat;
-        return units(lbmk::kTileTall) <= 1024 ? lbmk::kTileTall : lbmk::kTileNone;
+        // 300 x 100 in 7.8 us against 12.1 (Mid64), 2048 x 256 in 41.9 / 28.0 /
+        // 29.4, 8192 x 512 in 304 / 196 / 188
+        if (tiles(lbmk::kTileFlat64) <= 256) return lbmk::kTileFlat64;
+        return tiles(lbmk::kTileTall64) <= 1024 ? lbmk::kTileMid64 : lbmk::kTileTall64;
     }
-    if (units(lbmk::kTileFlat) <= 512) return lbmk::kTileFlat;
-    if (units(lbmk::kTileMid) <= 512) return lbmk::kTileMid;
-    return units(lbmk::kTileWide) <= 1024 ? lbmk::kTileWide : lbmk::kTileNone;
+    if (tiles(lbmk::kTileFlat) <= 512) return lbmk::kTileFlat;
+    return tiles(lbmk::kTileTall) <= kTallTiles ? lbmk::kTileMid : lbmk::kTileTall;
 }
 
-void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, Grid& g, int tile) {
+int tile_for(const lbm_params& p, int seg_rows) {
+    int t = p.precision == LBM_FP64 ? lbmk::kTileFlat64 : lbmk::kTileFlat;
+    for (int i = 0; i < 2 && lbmk::kTiles[t].own() < seg_rows; ++i) ++t;
+    return t;
+}
+
+void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, int tile, Grid& g) {
     g.Nx = p.Nx;
     g.Ny = p.Ny;
     g.pitch = L.pitch;
@@ -433,16 +430,14 @@ void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, Grid& g, int 
     g.open_x = (p.flags & LBM_OPEN_X) ? 1 : 0;
     g.y_first = g.periodic_y ? 0 : 1;
     g.plane = (unsigned)L.plane;
-    g.n_strips = (p.Nx + lbmk::kOwned - 1) / lbmk::kOwned;
     g.tile = tile;
-    if (tile != lbmk::kTileNone) seg_rows = lbmk::kTiles[tile].own();
-    g.seg_rows = std::max(1, std::min(seg_rows, g.rows));
+    g.seg_rows = balanced_rows(std::max(1, std::min(seg_rows, g.rows)), lbmk::kTiles[tile].own());
+    g.n_strips = strips_of(p);
     g.n_segs = (g.rows + g.seg_rows - 1) / g.seg_rows;
-    g.n_units = g.n_strips * g.n_segs;
-    const int nb = tile != lbmk::kTileNone
-                       ? g.n_units
-                       : (g.n_units + lbmk::kWavesPerBlock - 1) / lbmk::kWavesPerBlock;
-    g.n_blocks_pad = (nb + 7) / 8 * 8;
+    // chunks of strips per XCD only where the last one is not left nearly idle
+    g.strips_per_xcd = g.n_strips >= 32 ? (g.n_strips + 7) / 8 : 0;
+    g.n_blocks = g.strips_per_xcd ? 8 * g.strips_per_xcd * g.n_segs
+                                  : (g.n_strips * g.n_segs + 7) / 8 * 8;
 }
 
 void fill_phys(const lbm_params& p, Phys& k) {
@@ -456,17 +451,10 @@ void fill_phys(const lbm_params& p, Phys& k) {
     k.R = p.R;
     k.kappa = kap;
     k.inv_Tc = 1.0 / p.T_c;
-    k.inv_G = 1.0 / p.G;
-    k.negG = -p.G;
+    k.two_inv_G = 2.0 / p.G;
+    k.negG12 = -p.G / 12.0;
     k.psi_wall_eff = p.psi_w * p.G_w / p.G;
     k.Gw_psiw = p.G_w * p.psi_w;
-    k.c_e = 12.0 * p.theta / (1.0 / p.s_e - 0.5);
-    k.c_z = 12.0 * p.theta / (1.0 / p.s_zeta - 0.5);
-    k.s_rho = p.s_rho;
-    k.s_e = p.s_e;
-    k.s_z = p.s_zeta;
-    k.s_j = p.s_j;
-    k.s_q = p.s_q;
     k.tau_g = p.tau_g;
     k.dtau = p.tau_l - p.tau_g;
     k.rho_g = p.rho_g;
@@ -508,19 +496,22 @@ void fill_phys(const lbm_params& p, Phys& k) {
     k.flags = p.flags;
     auto fillr = [&](auto& r) {
         using T = std::remove_reference_t<decltype(r.b)>;
-        r.s_rho = (T)k.s_rho;
-        r.s_e = (T)k.s_e;
-        r.s_z = (T)k.s_z;
-        r.s_j = (T)k.s_j;
-        r.s_q = (T)k.s_q;
-        r.c_e = (T)k.c_e;
-        r.c_z = (T)k.c_z;
+        // s_zeta = s_e (validate() requires it); the conserved moments' rates
+        // s_rho and s_j drop out of the collision
+        r.se4 = (T)(0.25 * (1.0 - p.s_e));
+        r.se12 = (T)(p.s_e / 12.0);
+        r.se36 = (T)(p.s_e / 36.0);
+        r.q_u = (T)(p.s_e / 12.0);
+        r.q_F = (T)((1.0 - 0.5 * p.s_e) / 6.0);
+        r.q_th = (T)((1.0 - 0.5 * p.s_e) * (12.0 * p.theta / (1.0 / p.s_e - 0.5)) / 36.0);
+        r.xc = (T)(p.s_q / 12.0);
+        r.xd = (T)((3.0 - 2.0 * p.s_q) / 12.0);
         r.b = (T)k.b;
         r.rkA = (T)k.rkA;
         r.rkB1 = (T)k.rkB1;
         r.rkB2 = (T)k.rkB2;
         r.inv_Cv = (T)k.inv_Cv;
-        r.lambda = (T)k.lambda;
+        r.lam6 = (T)(k.lambda / 6.0);
         r.T_ref = (T)k.T_ref;
         r.dT_wall = (T)k.dT_wall;
         r.rho_ref = (T)k.rho_ref;
@@ -540,14 +531,18 @@ void fill_phys(const lbm_params& p, Phys& k) {
 
 namespace {
 
-using lbmhost::default_seg_rows;
-
-void set_grid(lbm_sim* s, int seg_rows, int tile = lbmk::kTileNone) {
-    lbmhost::fill_grid(s->p, s->L, seg_rows, s->g, tile);
-    s->seg_rows = s->g.seg_rows;
-}
-void set_default_grid(lbm_sim* s) {
-    set_grid(s, default_seg_rows(s->p, s->L.rows), lbmhost::default_tile(s->p, s->L.rows));
+// segments of seg_rows rows (> 0), or the default shape
+void set_grid(lbm_sim* s, int seg_rows) {
+    int tile;
+    if (seg_rows > 0) {
+        s->seg_rows = std::min(seg_rows, s->L.rows);
+        tile = lbmhost::tile_for(s->p, s->seg_rows);
+    } else {
+        tile = lbmhost::default_tile(s->p, s->L.rows);
+        s->seg_rows = lbmhost::balanced_rows(s->L.rows, lbmk::kTiles[tile].own());
+    }
+    s->seg_arg = seg_rows > 0 ? seg_rows : 0;
+    lbmhost::fill_grid(s->p, s->L, s->seg_rows, tile, s->g);
 }
 
 void set_phys(lbm_sim* s) { lbmhost::fill_phys(s->p, s->k); }
@@ -806,7 +801,7 @@ lbm_status lbm_create(const lbm_params* pin, const double* rho0, void* workspace
         s->owns_stream = true;
     }
     set_phys(s);
-    set_default_grid(s);
+    set_grid(s, 0);
     // zero everything (pitch padding stays zero), upload rho0, start state
     e = hipMemsetAsync(s->base, 0, s->L.total, s->stream);
     if (e == hipSuccess)
@@ -980,25 +975,24 @@ lbm_status lbm_load(lbm_sim* s, const void* host, size_t bytes) {
     HIPCHK(hipMemsetAsync(s->stat(), 0, lbmhost::kStatWords * sizeof(unsigned long long),
                           s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
-    const int seg = s->seg_rows, tile = s->g.tile;
+    const int seg = s->seg_arg;
     s->p = h.p;
     s->n = h.n;
     set_phys(s);
-    set_grid(s, seg, tile);
+    set_grid(s, seg);
     return LBM_OK;
 }
 
 lbm_status lbm_set_launch(lbm_sim* s, int32_t seg_rows) {
     if (!s) return fail(LBM_EINVAL, "null sim");
-    if (seg_rows > 0) set_grid(s, seg_rows);
-    else set_default_grid(s);
+    set_grid(s, seg_rows);
     return LBM_OK;
 }
 
 lbm_status lbm_get_launch(const lbm_sim* s, int32_t* seg_rows, int32_t* waves) {
     if (!s) return fail(LBM_EINVAL, "null sim");
-    if (seg_rows) *seg_rows = s->g.seg_rows;
-    if (waves) *waves = s->g.n_units;
+    if (seg_rows) *seg_rows = s->seg_rows;
+    if (waves) *waves = s->g.n_strips * ((s->L.rows + s->seg_rows - 1) / s->seg_rows);
     return LBM_OK;
 }
 
@@ -1039,33 +1033,17 @@ lbm_status lbm_autotune(lbm_sim* s, int32_t steps_per_trial, double* best_ms) {
     if (e == hipSuccess && lb)
         e = hipMemcpyAsync(snap + fb + tb, s->base + s->L.off_lo[f0], lb, hipMemcpyDeviceToDevice,
                            s->stream);
-    // segment heights with seg + 10 (the recomputed halo rows) a multiple of
-    // the kernel's six-row unroll, so full segments need no padding rows
-    std::vector<int> cands;
-    for (int c = 2; c <= 128; c += 6)
-        if (c <= s->L.rows) cands.push_back(c);
-    for (int c : {152, 188, 248, 506})
-        if (c <= s->L.rows) cands.push_back(c);
-    cands.push_back(s->L.rows);
-    cands.push_back(default_seg_rows(s->p, s->L.rows));
-    std::sort(cands.begin(), cands.end());
-    cands.erase(std::unique(cands.begin(), cands.end()), cands.end());
-    // the tile shapes, as the negative of their index
-    for (int t = 1; t < lbmk::kTileCount; ++t)
-        if ((t == lbmk::kTileTall) ? s->p.precision == LBM_FP64
-                                   : (t == lbmk::kTileFlat || s->p.precision != LBM_FP64))
-            cands.push_back(-t);
-    const auto take = [&](int c) {
-        if (c > 0) set_grid(s, c);
-        else set_grid(s, 0, -c);
-    };
+    // the default (0) and the heights up to the tallest tile
+    std::vector<int> cands = {0};
+    for (int c = 2; c <= 26; c += 2)
+        if (c < s->L.rows) cands.push_back(c);
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (e == hipSuccess) e = hipEventCreate(&ev0);
     if (e == hipSuccess) e = hipEventCreate(&ev1);
     double best = 1e300;
-    int best_seg = s->g.tile ? -s->g.tile : s->seg_rows;
+    int best_seg = s->seg_arg;
     for (size_t ci = 0; ci < cands.size() && e == hipSuccess; ++ci) {
-        take(cands[ci]);
+        set_grid(s, cands[ci]);
         for (int w = 0; w < 2 && e == hipSuccess; ++w) e = enqueue_step(s);
         if (e == hipSuccess) e = hipEventRecord(ev0, s->stream);
         for (int i = 0; i < steps_per_trial && e == hipSuccess; ++i) e = enqueue_step(s);
@@ -1085,7 +1063,7 @@ lbm_status lbm_autotune(lbm_sim* s, int32_t steps_per_trial, double* best_ms) {
     if (ev0) (void)hipEventDestroy(ev0);
     if (ev1) (void)hipEventDestroy(ev1);
     (void)hipFree(snap);
-    take(best_seg);
+    set_grid(s, best_seg);
     if (e != hipSuccess) return fail(LBM_EDEVICE, "autotune: %s", hipGetErrorString(e));
     if (best_ms) *best_ms = best;
     return LBM_OK;

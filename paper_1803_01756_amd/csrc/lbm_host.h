@@ -27,13 +27,34 @@ constexpr size_t kPlaneSkew = 832;
 struct Layout {
     int pitch, rows;
     size_t plane, esz;
-    size_t off_f[2], off_lo[2], off_T[2], off_mom, off_scr, off_part, off_out, off_stat, total;
+    size_t off_f[2], off_lo[2], off_T[2], off_mom, off_part, off_out, off_stat, total;
 };
 
-// Health counters of a channel (unsigned 64-bit, device memory): the two
-// the step kernels add to (non-finite readings, psi clamps) and the count
-// of non-finite nodes found by the last read-out.
-enum { kStatNonfinite = 0, kStatClamps = 1, kStatReadout = 2, kStatWords = 4 };
+// Health counters of a channel (unsigned 64-bit, device memory) that the step
+// kernels add to: non-finite readings, psi clamps.
+enum { kStatNonfinite = 0, kStatClamps = 1, kStatWords = lbmk::kStepWords };
+
+// Pinned host memory for a read-out of Nx x Ny nodes (grown, never shrunk;
+// null members while none is held).
+struct ReadoutMem {
+    lbmk::Readout ro = {nullptr, nullptr};
+    int cap = 0;  // workgroups it holds
+};
+hipError_t reserve_readout(ReadoutMem& m, int Nx, int Ny);
+void free_readout(ReadoutMem& m);
+// Fluid nodes found not finite by the last read-out of Nx x Ny nodes.
+unsigned long long readout_bad(const ReadoutMem& m, int Nx, int Ny);
+
+// Where a read-out writes its fields: an array of the caller's that lies in
+// pinned host memory as a whole is written by the kernel itself, any other is
+// copied from the device array that stands for it.
+struct ReadoutPlan {
+    lbmk::Moments direct;  // what the kernel writes
+    double* copy_to[4];    // host arrays to copy to afterwards (null: none)
+    double* copy_from[4];
+};
+ReadoutPlan plan_readout(double* const host[4], double* const dev[4], size_t cells);
+hipError_t enqueue_copies(const ReadoutPlan& r, size_t cells, hipStream_t s);
 
 lbm_status fail(lbm_status st, const char* fmt, ...);
 bool make_layout(const lbm_params& p, Layout* L);

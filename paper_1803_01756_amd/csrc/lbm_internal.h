@@ -142,16 +142,26 @@ struct Slot {
 hipError_t launch_step_batched(const Slot* slots, int n_slots, int total_blocks, int tile,
                                int step_i, bool ext, hipStream_t s);
 
-// rho, u (half force) and T at the current time level into device arrays of
-// Nx*Ny doubles; work holds 3*Nx*Ny doubles; *n_bad is incremented for
-// every fluid node whose rho or T is not finite.
+// rho, u (half force) and T at the current time level into arrays of Nx*Ny
+// doubles in memory that the device can write (any may be null).
+struct Moments {
+    double *rho, *ux, *uy, *T;
+};
+// Pinned host memory that a read-out fills: the channel's kStepWords health
+// counters, and for each of its readout_blocks workgroups the number of fluid
+// nodes whose rho or T is not finite.
+constexpr int kStepWords = 2;
+struct Readout {
+    unsigned long long* words;
+    unsigned* bad;
+};
+int readout_blocks(int Nx, int Ny);
 hipError_t launch_moments_f32(const Grid& g, const Phys& k, const float* f, const float* f0lo,
-                              const float* T, double* work, double* rho, double* ux,
-                              double* uy, double* Tout, int64_t n, unsigned long long* n_bad,
-                              hipStream_t s);
+                              const float* T, const Moments& out, int64_t n,
+                              const unsigned long long* stat, const Readout& ro, hipStream_t s);
 hipError_t launch_moments_f64(const Grid& g, const Phys& k, const double* f, const double* T,
-                              double* work, double* rho, double* ux, double* uy,
-                              double* Tout, int64_t n, unsigned long long* n_bad, hipStream_t s);
+                              const Moments& out, int64_t n, const unsigned long long* stat,
+                              const Readout& ro, hipStream_t s);
 
 // Rest-equilibrium start from a device density field rho0 (Nx*Ny doubles).
 hipError_t launch_init_f32(const Grid& g, const Phys& k, const double* rho0, float* f,

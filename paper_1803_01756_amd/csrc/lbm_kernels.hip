@@ -1038,15 +1038,15 @@ void step_batched_kernel(const Slot* __restrict__ slots, int n_slots, int step_i
     step_tile<float, false, kExt, kRows, kWaves>(g, k, B, n, strip, seg, L);
 }
 
-// ---- moments: two passes over all nodes ------------------------------------
+// ---- moments ----------------------------------------------------------------
 // a node of a FRAME_RHO reservoir (y counts the plate rows)
 __device__ __forceinline__ bool reservoir_node(const Grid& g, int cx, int y) {
     return g.frame_rho &&
            (cx == 0 || cx == g.Nx - 1 || (g.periodic_y && (y == 0 || y == g.Ny - 1)));
 }
 
-// The read-out's arithmetic per node, shared by the two-pass read-out and
-// the one-pass reduction, so that both see bitwise the same node values.
+// The read-out's arithmetic per node, shared by the read-out and the
+// one-pass reduction, so that both see bitwise the same node values.
 struct NodeState {
     double rho, psi, jx, jy, T;  // rho = 0 and j = 0 on plate rows
     bool fluid;
@@ -1135,59 +1135,97 @@ __device__ __forceinline__ int read_xp(const Grid& g, int cx) {
     return cx == g.Nx - 1 ? (g.open_x ? cx : 0) : cx + 1;
 }
 
-// pass 1: rho, psi, j (and T) per node into scratch; pass 2: forces and u.
-template <class S, bool kMX>
-__global__ __launch_bounds__(256) void moments_pass1(Grid g, Phys k, const S* __restrict__ f,
-                                                     const float* __restrict__ f0lo,
-                                                     const S* __restrict__ T,
-                                                     double* __restrict__ work,
-                                                     double* __restrict__ rho_out,
-                                                     double* __restrict__ T_out, long long n_t,
-                                                     unsigned long long* __restrict__ n_bad) {
-    const int n = g.Nx * g.Ny;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int y = i / g.Nx, cx = i - y * g.Nx;
-    const NodeState o = node_state<S, kMX>(g, k, f, f0lo, T, cx, y, n_t);
-    work[i] = o.psi;
-    work[n + i] = o.jx;
-    work[2 * n + i] = o.jy;
-    rho_out[i] = o.rho;
-    T_out[i] = o.T;
-    if (o.fluid && !(__builtin_isfinite(o.rho) && __builtin_isfinite(o.T))) atomicAdd(n_bad, 1ull);
-}
+// rho, u and T of every node.  A workgroup takes 64 columns of 4 x kReadRows
+// rows: each wave evaluates its own kReadRows rows (kept in registers but for
+// psi), the ring of one node around the block goes round in one more
+// evaluation by the first threads, and u follows from the psi in LDS.  The
+// outputs may be device memory or pinned host memory: a wave's stores of 64
+// consecutive doubles cross the link at the rate of the copy engine from some
+// 2 MB on (44 GB/s at 2.5 MB, 54 at 17, 56 at 134, the link's), and below that
+// one launch that writes the host arrays (13 us for 128 x 32) stands for a
+// clearing, two passes over the nodes with psi and j between them in memory,
+// and five copies (95 us).
+// Non-finite nodes are counted per workgroup into bad[], every entry written
+// on each launch, and the step's counters go along into words[]: both pinned
+// host memory, so that the read-out needs no copy of its own for them.
+constexpr int kReadRows = 2;
+constexpr int kReadW = 64, kReadH = 4 * kReadRows;
 
-__global__ __launch_bounds__(256) void moments_pass2(Grid g, Phys k,
-                                                     const double* __restrict__ work,
-                                                     const double* __restrict__ rho_in,
-                                                     double* __restrict__ ux_out,
-                                                     double* __restrict__ uy_out, long long n_t) {
-    const int n = g.Nx * g.Ny;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int y = i / g.Nx, cx = i - y * g.Nx;
-    const RowK r = row_info(y, g);
-    if (!r.fluid) {
-        ux_out[i] = uy_out[i] = 0.0;
-        return;
+template <class S, bool kMX>
+__global__ __launch_bounds__(256) void moments_kernel(Grid g, Phys k, const S* __restrict__ f,
+                                                      const float* __restrict__ f0lo,
+                                                      const S* __restrict__ T, Moments out,
+                                                      long long n_t,
+                                                      const unsigned long long* __restrict__ stat,
+                                                      Readout ro) {
+    __shared__ double psi_t[kReadH + 2][kReadW + 2];
+    __shared__ unsigned cnt[4];
+    const int tiles_x = (g.Nx + kReadW - 1) / kReadW;
+    const int x0 = ((int)blockIdx.x % tiles_x) * kReadW, y0 = ((int)blockIdx.x / tiles_x) * kReadH;
+    const int tx = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (blockIdx.x == 0 && threadIdx.x < kStepWords) ro.words[threadIdx.x] = stat[threadIdx.x];
+    const int cx = x0 + tx;
+    NodeState o[kReadRows];
+    unsigned bad = 0;
+#pragma unroll
+    for (int i = 0; i < kReadRows; ++i) {
+        const int ey = wv * kReadRows + i, y = y0 + ey;
+        const bool in = cx < g.Nx && y < g.Ny;
+        if (in) {
+            o[i] = node_state<S, kMX>(g, k, f, f0lo, T, cx, y, n_t);
+            psi_t[ey + 1][tx + 1] = o[i].psi;
+        }
+        bad += __popcll(__ballot(in && o[i].fluid &&
+                                 !(__builtin_isfinite(o[i].rho) && __builtin_isfinite(o[i].T))));
     }
-    const double* psi = work;
-    const double* jx = work + n;
-    const double* jy = work + 2 * n;
-    const int xm = read_xm(g, cx), xp = read_xp(g, cx);
-    int ys = y - 1, yn = y + 1;
-    if (g.periodic_y) {
-        if (ys < 0) ys += g.Ny;
-        if (yn >= g.Ny) yn -= g.Ny;
+    if (tx == 0) cnt[wv] = bad;
+    // the ring; past the last column or row of the grid the block's own
+    // entries there are the ring's (periodic image or, past an open end, the
+    // end column itself); entries that no node reads are left unset
+    {
+        constexpr int kRow = kReadW + 2, kRing = 2 * kRow + 2 * kReadH;
+        static_assert(kRing <= 256, "one ring node per thread");
+        const int t = threadIdx.x;
+        int ex, ey;
+        if (t < 2 * kRow) {
+            ey = t < kRow ? 0 : kReadH + 1;
+            ex = t < kRow ? t : t - kRow;
+        } else {
+            ey = 1 + ((t - 2 * kRow) >> 1);
+            ex = (t & 1) ? kReadW + 1 : 0;
+        }
+        // the ring's far side moves in to the grid's last column and row
+        if (ex == kReadW + 1) ex = min(ex, g.Nx - x0 + 1);
+        if (ey == kReadH + 1) ey = min(ey, g.Ny - y0 + 1);
+        int rx = x0 - 1 + ex, y = y0 - 1 + ey;
+        if (rx < 0) rx = read_xm(g, 0);
+        else if (rx >= g.Nx) rx = rx == g.Nx ? read_xp(g, g.Nx - 1) : -1;
+        if (g.periodic_y) y = y < 0 ? y + g.Ny : (y >= g.Ny ? (y == g.Ny ? 0 : -1) : y);
+        else if (y >= g.Ny) y = -1;
+        if (t < kRing && rx >= 0 && y >= 0)
+            psi_t[ey][ex] = node_state<S, kMX>(g, k, f, f0lo, T, rx, y, n_t).psi;
     }
-    auto row3 = [&](int yy) {
-        return tri_of(psi[yy * g.Nx + cx], psi[yy * g.Nx + xm], psi[yy * g.Nx + xp]);
-    };
-    double ux, uy;
-    node_velocity(g, k, cx, y, row3(ys), row3(y), row3(yn), rho_in[i], jx[i], jy[i], n_t, ux,
-                  uy);
-    ux_out[i] = ux;
-    uy_out[i] = uy;
+    __syncthreads();
+    if (threadIdx.x == 0) ro.bad[blockIdx.x] = (cnt[0] + cnt[1]) + (cnt[2] + cnt[3]);
+    if (cx >= g.Nx) return;
+#pragma unroll
+    for (int i = 0; i < kReadRows; ++i) {
+        const int ey = wv * kReadRows + i, y = y0 + ey;
+        if (y >= g.Ny) return;
+        double ux = 0.0, uy = 0.0;
+        if (o[i].fluid) {
+            auto row3 = [&](int e) {
+                return tri_of(psi_t[e][tx + 1], psi_t[e][tx], psi_t[e][tx + 2]);
+            };
+            node_velocity(g, k, cx, y, row3(ey), row3(ey + 1), row3(ey + 2), o[i].rho, o[i].jx,
+                          o[i].jy, n_t, ux, uy);
+        }
+        const size_t at = (size_t)y * g.Nx + cx;
+        if (out.rho) out.rho[at] = o[i].rho;
+        if (out.ux) out.ux[at] = ux;
+        if (out.uy) out.uy[at] = uy;
+        if (out.T) out.T[at] = o[i].T;
+    }
 }
 
 // ---- initial state ----------------------------------------------------------
@@ -1456,32 +1494,30 @@ hipError_t launch_step_batched(const Slot* slots, int n_slots, int total_blocks,
                : batched_impl<false>(slots, n_slots, total_blocks, tile, step_i, s);
 }
 
+int readout_blocks(int Nx, int Ny) {
+    return ((Nx + kReadW - 1) / kReadW) * ((Ny + kReadH - 1) / kReadH);
+}
+
 template <class S, bool kMX>
 static hipError_t moments_impl(const Grid& g, const Phys& k, const S* f, const float* f0lo,
-                               const S* T, double* work, double* rho, double* ux, double* uy,
-                               double* Tout, int64_t n_t, unsigned long long* n_bad,
+                               const S* T, const Moments& out, int64_t n_t,
+                               const unsigned long long* stat, const Readout& ro,
                                hipStream_t s) {
-    const int n = g.Nx * g.Ny;
-    hipLaunchKernelGGL((moments_pass1<S, kMX>), dim3(blocks_for(n, 256)), dim3(256), 0, s, g, k,
-                       f, f0lo, T, work, rho, Tout, (long long)n_t, n_bad);
-    hipLaunchKernelGGL(moments_pass2, dim3(blocks_for(n, 256)), dim3(256), 0, s, g, k,
-                       (const double*)work, (const double*)rho, ux, uy, (long long)n_t);
+    hipLaunchKernelGGL((moments_kernel<S, kMX>), dim3(readout_blocks(g.Nx, g.Ny)), dim3(256), 0, s,
+                       g, k, f, f0lo, T, out, (long long)n_t, stat, ro);
     return hipGetLastError();
 }
 
 hipError_t launch_moments_f32(const Grid& g, const Phys& k, const float* f, const float* f0lo,
-                              const float* T, double* work, double* rho, double* ux,
-                              double* uy, double* Tout, int64_t n, unsigned long long* n_bad,
-                              hipStream_t s) {
-    if (f0lo)
-        return moments_impl<float, true>(g, k, f, f0lo, T, work, rho, ux, uy, Tout, n, n_bad, s);
-    return moments_impl<float, false>(g, k, f, nullptr, T, work, rho, ux, uy, Tout, n, n_bad, s);
+                              const float* T, const Moments& out, int64_t n,
+                              const unsigned long long* stat, const Readout& ro, hipStream_t s) {
+    if (f0lo) return moments_impl<float, true>(g, k, f, f0lo, T, out, n, stat, ro, s);
+    return moments_impl<float, false>(g, k, f, nullptr, T, out, n, stat, ro, s);
 }
 hipError_t launch_moments_f64(const Grid& g, const Phys& k, const double* f, const double* T,
-                              double* work, double* rho, double* ux, double* uy,
-                              double* Tout, int64_t n, unsigned long long* n_bad, hipStream_t s) {
-    return moments_impl<double, false>(g, k, f, nullptr, T, work, rho, ux, uy, Tout, n, n_bad,
-                                       s);
+                              const Moments& out, int64_t n, const unsigned long long* stat,
+                              const Readout& ro, hipStream_t s) {
+    return moments_impl<double, false>(g, k, f, nullptr, T, out, n, stat, ro, s);
 }
 
 hipError_t launch_init_f32(const Grid& g, const Phys& k, const double* rho0, float* f,

@@ -57,7 +57,7 @@ struct SlotState {
 };
 
 // words per slot in the health-counter array: non-finite readings, clamps
-constexpr int kSlotStat = 2;
+constexpr int kSlotStat = lbmk::kStepWords;
 
 // Buckets of fluid rows for the tuned launch shapes: up to 32, 64, 128, 256
 // rows, and more.
@@ -99,12 +99,12 @@ struct lbm_pool {
     lbmk::Slot* table_host[2] = {nullptr, nullptr};
     hipEvent_t table_free[2] = {nullptr, nullptr};
     int table_cap = 0, table_next = 0;
-    // moment scratch on the aux stream: 7 doubles per node of the largest slot
+    // moment arrays on the aux stream: 4 doubles per node of the largest slot
     double* mom = nullptr;
     size_t mom_cells = 0;
+    lbmhost::ReadoutMem ro;
     // health counters: kSlotStat words per slot id on the device (the step
-    // adds to them), mirrored into pinned host memory after every chunk; the
-    // last word of the array counts non-finite nodes of a read-out
+    // adds to them), mirrored into pinned host memory after every chunk
     unsigned long long* stat_dev = nullptr;
     unsigned long long* stat_host = nullptr;
     int stat_cap = 0;
@@ -141,19 +141,18 @@ lbm_status ensure_mom(lbm_pool* P, size_t cells) {
     PCHK(hipStreamSynchronize(P->aux));
     if (P->mom) PCHK(hipFree(P->mom));
     P->mom = nullptr;
-    PCHK(hipMalloc(reinterpret_cast<void**>(&P->mom), cells * 7 * sizeof(double)));
+    PCHK(hipMalloc(reinterpret_cast<void**>(&P->mom), cells * 4 * sizeof(double)));
     P->mom_cells = cells;
     return LBM_OK;
 }
 
-// Room for the counters of slot ids 0..n-1 (plus the read-out word); a
-// larger array is filled from the old one while no stream uses it.
+// Room for the counters of slot ids 0..n-1; a larger array is filled from the old one while no stream uses it.
 lbm_status ensure_stat(lbm_pool* P, int n) {
     if (n <= P->stat_cap) return LBM_OK;
     PCHK(hipStreamSynchronize(P->main));
     PCHK(hipStreamSynchronize(P->aux));
     const int cap = std::max(n, std::max(64, 2 * P->stat_cap));
-    const size_t words = (size_t)cap * kSlotStat + 1;
+    const size_t words = (size_t)cap * kSlotStat;
     unsigned long long *d = nullptr, *h = nullptr;
     PCHK(hipMalloc(reinterpret_cast<void**>(&d), words * sizeof(*d)));
     hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&h), words * sizeof(*h),
@@ -268,6 +267,8 @@ lbm_status lbm_pool_admit(lbm_pool* P, const lbm_params* pin, const double* rho0
     PCHK(hipSetDevice(P->dev));
     st = ensure_mom(P, cells);
     if (st != LBM_OK) return st;
+    // (no read-out is under way: lbm_pool_moments returns with its results)
+    PCHK(lbmhost::reserve_readout(P->ro, p.Nx, p.Ny));
 
     int id = -1;
     for (size_t i = 0; i < P->slots.size(); ++i)
@@ -495,25 +496,20 @@ lbm_status lbm_pool_moments(lbm_pool* P, int32_t id, double* rho, double* ux, do
     PCHK(hipStreamWaitEvent(P->aux, s->ready, 0));
     PCHK(hipStreamWaitEvent(P->aux, s->done, 0));
     const size_t cells = (size_t)s->p.Nx * s->p.Ny;
-    double* m = P->mom;
-    unsigned long long* nb = P->stat_dev + (size_t)P->stat_cap * kSlotStat;
-    PCHK(hipMemsetAsync(nb, 0, sizeof(*nb), P->aux));
-    PCHK(lbmk::launch_moments_f32(s->g, s->k, s->f[s->cur_f], nullptr, s->T[s->cur_T], m + 4 * cells,
-                                  m, m + cells, m + 2 * cells, m + 3 * cells, s->n, nb, P->aux));
-    double* outs[4] = {rho, ux, uy, T};
-    for (int q = 0; q < 4; ++q)
-        if (outs[q])
-            PCHK(hipMemcpyAsync(outs[q], m + q * cells, cells * sizeof(double),
-                                hipMemcpyDeviceToHost, P->aux));
-    unsigned long long st[kSlotStat + 1];
-    PCHK(hipMemcpyAsync(st, P->stat_dev + (size_t)id * kSlotStat,
-                        kSlotStat * sizeof(unsigned long long), hipMemcpyDeviceToHost, P->aux));
-    PCHK(hipMemcpyAsync(st + kSlotStat, nb, sizeof(*nb), hipMemcpyDeviceToHost, P->aux));
+    double* const outs[4] = {rho, ux, uy, T};
+    double* const dev[4] = {P->mom, P->mom + cells, P->mom + 2 * cells, P->mom + 3 * cells};
+    const lbmhost::ReadoutPlan plan = lbmhost::plan_readout(outs, dev, cells);
+    PCHK(lbmk::launch_moments_f32(s->g, s->k, s->f[s->cur_f], nullptr, s->T[s->cur_T],
+                                  plan.direct, s->n, P->stat_dev + (size_t)id * kSlotStat,
+                                  P->ro.ro, P->aux));
+    PCHK(lbmhost::enqueue_copies(plan, cells, P->aux));
     PCHK(hipStreamSynchronize(P->aux));
-    if (st[0] || st[kSlotStat])
+    const unsigned long long read = P->ro.ro.words[0],
+                             now = lbmhost::readout_bad(P->ro, s->p.Nx, s->p.Ny);
+    if (read || now)
         return fail(LBM_EUNSTABLE,
                     "slot %d: non-finite state (%llu node readings by its steps up to n = %lld, "
-                    "%llu nodes at the read-out)%s", id, st[0], (long long)s->n, st[kSlotStat],
+                    "%llu nodes at the read-out)%s", id, read, (long long)s->n, now,
                     s->failed ? "; retired before its last step" : "");
     return LBM_OK;
 }
@@ -567,6 +563,7 @@ lbm_status lbm_pool_destroy(lbm_pool* P) {
     for (hipEvent_t ev : P->spare_events) (void)hipEventDestroy(ev);
     if (P->table_dev) (void)hipFree(P->table_dev);
     if (P->mom) (void)hipFree(P->mom);
+    lbmhost::free_readout(P->ro);
     if (P->stat_dev) (void)hipFree(P->stat_dev);
     if (P->stat_host) (void)hipHostFree(P->stat_host);
     if (P->aux) (void)hipStreamDestroy(P->aux);

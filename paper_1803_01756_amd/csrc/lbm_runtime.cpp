@@ -255,8 +255,6 @@ bool make_layout(const lbm_params& p, Layout* L) {
     if (o >= ((size_t)1 << 32) - kAlign) return false;
     L->off_mom = o;
     o = align_up(o + 4 * cells * sizeof(double));
-    L->off_scr = o;
-    o = align_up(o + 3 * cells * sizeof(double));
     L->off_part = o;
     o = align_up(o + lbmk::kReduceBlocks * 5 * sizeof(double));
     L->off_out = o;
@@ -361,6 +359,7 @@ struct lbm_sim {
     int fcur = 0, tcur = 0;
     int seg_rows = 0;  // rows of a segment (a tile or several)
     int seg_arg = 0;   // the height asked for, 0: default
+    lbmhost::ReadoutMem ro;
 
     template <class S>
     S* f(int b) const { return reinterpret_cast<S*>(base + L.off_f[b]); }
@@ -373,7 +372,6 @@ struct lbm_sim {
     double* mom(int q) const {
         return reinterpret_cast<double*>(base + L.off_mom) + (size_t)q * p.Nx * p.Ny;
     }
-    double* scr() const { return reinterpret_cast<double*>(base + L.off_scr); }
     double* part() const { return reinterpret_cast<double*>(base + L.off_part); }
     double* out() const { return reinterpret_cast<double*>(base + L.off_out); }
     unsigned long long* stat() const {
@@ -382,6 +380,79 @@ struct lbm_sim {
 };
 
 namespace lbmhost {
+
+hipError_t reserve_readout(ReadoutMem& m, int Nx, int Ny) {
+    if (lbmk::readout_blocks(Nx, Ny) <= m.cap) return hipSuccess;
+    const int n = std::max(lbmk::readout_blocks(Nx, Ny), 2 * m.cap);
+    free_readout(m);
+    void* p = nullptr;
+    const hipError_t e = hipHostMalloc(&p, kStatWords * sizeof(unsigned long long) +
+                                               n * sizeof(unsigned), hipHostMallocDefault);
+    if (e != hipSuccess) return e;
+    m.ro.words = static_cast<unsigned long long*>(p);
+    m.ro.bad = reinterpret_cast<unsigned*>(m.ro.words + kStatWords);
+    m.cap = n;
+    return hipSuccess;
+}
+
+void free_readout(ReadoutMem& m) {
+    if (m.ro.words) (void)hipHostFree(m.ro.words);
+    m = ReadoutMem();
+}
+
+unsigned long long readout_bad(const ReadoutMem& m, int Nx, int Ny) {
+    unsigned long long n = 0;
+    for (int b = 0, nb = lbmk::readout_blocks(Nx, Ny); b < nb; ++b) n += m.ro.bad[b];
+    return n;
+}
+
+// The device address of a host array that is pinned from its first to its
+// last byte (null for any other memory).
+static double* pinned_view(double* p, size_t bytes) {
+    if (reinterpret_cast<uintptr_t>(p) % sizeof(double) != 0) return nullptr;
+    hipPointerAttribute_t a;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeHost ||
+        !a.devicePointer || hipMemGetAddressRange(&base, &size, a.devicePointer) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    const size_t at = static_cast<char*>(a.devicePointer) - static_cast<char*>(base);
+    return at <= size && bytes <= size - at ? static_cast<double*>(a.devicePointer) : nullptr;
+}
+
+ReadoutPlan plan_readout(double* const host[4], double* const dev[4], size_t cells) {
+    ReadoutPlan r = {};
+    double* to[4];
+    for (int q = 0; q < 4; ++q) {
+        to[q] = nullptr;
+        if (!host[q]) continue;
+        // arrays that overlap are copied, so that the last one named stands
+        bool alone = true;
+        for (int o = 0; o < 4; ++o)
+            alone = alone && (o == q || !host[o] || host[o] + cells <= host[q] ||
+                              host[q] + cells <= host[o]);
+        to[q] = alone ? pinned_view(host[q], cells * sizeof(double)) : nullptr;
+        if (!to[q]) {
+            to[q] = dev[q];
+            r.copy_to[q] = host[q];
+            r.copy_from[q] = dev[q];
+        }
+    }
+    r.direct = {to[0], to[1], to[2], to[3]};
+    return r;
+}
+
+hipError_t enqueue_copies(const ReadoutPlan& r, size_t cells, hipStream_t s) {
+    for (int q = 0; q < 4; ++q) {
+        if (!r.copy_to[q]) continue;
+        const hipError_t e = hipMemcpyAsync(r.copy_to[q], r.copy_from[q], cells * sizeof(double),
+                                            hipMemcpyDeviceToHost, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 int balanced_rows(int rows, int target) {
     const int segs = std::max(1, (rows + target - 1) / target);
@@ -571,18 +642,14 @@ hipError_t enqueue_step(lbm_sim* s) {
     return hipSuccess;
 }
 
-// The read-out's count of non-finite nodes restarts at every read-out.
-hipError_t enqueue_moments(lbm_sim* s) {
-    unsigned long long* nb = s->stat() + lbmhost::kStatReadout;
-    hipError_t e = hipMemsetAsync(nb, 0, sizeof(*nb), s->stream);
-    if (e != hipSuccess) return e;
+// Enqueues the read-out into `out`; the counters land in s->ro.
+hipError_t enqueue_moments(lbm_sim* s, const lbmk::Moments& out) {
     if (s->p.precision == LBM_FP64)
         return lbmk::launch_moments_f64(s->g, s->k, s->f<double>(s->fcur), s->T<double>(s->tcur),
-                                        s->scr(), s->mom(0), s->mom(1), s->mom(2), s->mom(3),
-                                        s->n, nb, s->stream);
+                                        out, s->n, s->stat(), s->ro.ro, s->stream);
     return lbmk::launch_moments_f32(s->g, s->k, s->f<float>(s->fcur), s->lo(s->fcur),
-                                    s->T<float>(s->tcur), s->scr(), s->mom(0), s->mom(1),
-                                    s->mom(2), s->mom(3), s->n, nb, s->stream);
+                                    s->T<float>(s->tcur), out, s->n, s->stat(), s->ro.ro,
+                                    s->stream);
 }
 
 // Host copy of the health counters, enqueued on the stream (the caller
@@ -596,7 +663,7 @@ hipError_t enqueue_stat_copy(lbm_sim* s, unsigned long long* host) {
 // non-finite state or the read-out found one; LBM_OK otherwise.
 lbm_status health_status(const lbm_sim* s, const unsigned long long* st, bool readout) {
     const unsigned long long bad = st[lbmhost::kStatNonfinite],
-                             now = readout ? st[lbmhost::kStatReadout] : 0ull;
+                             now = readout ? lbmhost::readout_bad(s->ro, s->p.Nx, s->p.Ny) : 0ull;
     if (bad || now)
         return fail(LBM_EUNSTABLE,
                     "non-finite state: %llu node readings by the steps up to n = %lld, "
@@ -802,6 +869,12 @@ lbm_status lbm_create(const lbm_params* pin, const double* rho0, void* workspace
     }
     set_phys(s);
     set_grid(s, 0);
+    e = lbmhost::reserve_readout(s->ro, p.Nx, p.Ny);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        lbm_destroy(s);
+        return fail(LBM_ENOMEM, "pinned host memory: %s", hipGetErrorString(e));
+    }
     // zero everything (pitch padding stays zero), upload rho0, start state
     e = hipMemsetAsync(s->base, 0, s->L.total, s->stream);
     if (e == hipSuccess)
@@ -844,31 +917,27 @@ lbm_status lbm_synchronize(lbm_sim* s) {
 lbm_status lbm_moments(lbm_sim* s, double* rho, double* ux, double* uy, double* T) {
     if (!s) return fail(LBM_EINVAL, "null sim");
     HIPCHK(hipSetDevice(s->dev));
-    HIPCHK(enqueue_moments(s));
-    double* outs[4] = {rho, ux, uy, T};
-    const size_t bytes = (size_t)s->p.Nx * s->p.Ny * sizeof(double);
-    for (int q = 0; q < 4; ++q)
-        if (outs[q])
-            HIPCHK(hipMemcpyAsync(outs[q], s->mom(q), bytes, hipMemcpyDeviceToHost, s->stream));
-    unsigned long long st[lbmhost::kStatWords];
-    HIPCHK(enqueue_stat_copy(s, st));
+    double* const outs[4] = {rho, ux, uy, T};
+    double* const dev[4] = {s->mom(0), s->mom(1), s->mom(2), s->mom(3)};
+    const size_t cells = (size_t)s->p.Nx * s->p.Ny;
+    const lbmhost::ReadoutPlan plan = lbmhost::plan_readout(outs, dev, cells);
+    HIPCHK(enqueue_moments(s, plan.direct));
+    HIPCHK(lbmhost::enqueue_copies(plan, cells, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
-    return health_status(s, st, true);
+    return health_status(s, s->ro.ro.words, true);
 }
 
 lbm_status lbm_reduce(lbm_sim* s, double out[5]) {
     if (!s || !out) return fail(LBM_EINVAL, "null argument");
     HIPCHK(hipSetDevice(s->dev));
-    HIPCHK(enqueue_moments(s));
+    HIPCHK(enqueue_moments(s, {s->mom(0), s->mom(1), s->mom(2), s->mom(3)}));
     HIPCHK(lbmk::launch_reduce(s->mom(0), s->mom(1), s->mom(2), s->mom(3), s->p.Nx * s->p.Ny,
                                s->p.C_v, s->part(), s->out(), s->stream));
     HIPCHK(hipMemcpyAsync(out, s->out(), 5 * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-    unsigned long long st[lbmhost::kStatWords];
-    HIPCHK(enqueue_stat_copy(s, st));
     HIPCHK(hipStreamSynchronize(s->stream));
     if (out[4] > 0.0) return fail(LBM_EUNSTABLE, "%g non-finite nodes at n = %lld", out[4],
                                   (long long)s->n);
-    return health_status(s, st, true);
+    return health_status(s, s->ro.ro.words, true);
 }
 
 lbm_status lbm_reduce_noalloc(lbm_sim* s, double* out_dev) {
@@ -903,6 +972,7 @@ lbm_status lbm_destroy(lbm_sim* s) {
     (void)hipSetDevice(s->dev);
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     if (s->owns_mem && s->base) (void)hipFree(s->base);
+    lbmhost::free_readout(s->ro);
     if (s->owns_stream && s->stream) (void)hipStreamDestroy(s->stream);
     delete s;
     return LBM_OK;

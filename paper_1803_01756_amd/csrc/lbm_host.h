@@ -68,6 +68,8 @@ constexpr long long kTallTiles = 2048;
 // The tile shape of a channel stepped alone by default, and the smallest one
 // that holds seg_rows rows (the tallest if none does).
 int default_tile(const lbm_params& p, int rows);
+// Rows of a segment of a channel stepped alone by default, in that tile.
+int default_rows(const lbm_params& p, int rows, int tile);
 int tile_for(const lbm_params& p, int seg_rows);
 // Grid of a launch with segments of seg_rows rows in tiles of shape `tile`:
 // segments taller than a tile are split evenly.

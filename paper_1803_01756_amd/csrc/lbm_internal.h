@@ -55,12 +55,15 @@ struct Phys {
     double Gw_psiw;                     // G_w psi_w (Eq. 14 on the wall rows)
     double tau_g, dtau, rho_g, inv_drho;// Eq. 5 (inv_drho = 0: constant tau)
     double inv_Cv, lambda;              // Eq. 16
-    double g_osc, period;               // drive g_osc sin(2 pi n / period) along +x
+    double g_osc, period, inv_period;   // drive g_osc sin(2 pi n / period) along +x
     double g_x, g_y, rho_v;             // Eq. 15
     double rho_frame;                   // reservoir density of a frame
-    double p0, p_amp, p_period;         // open ends: inlet pressure p0 (1 + p_amp sin(...))
-    double T_in_eos;                    // temperature of the boundary EOS pressures
-    double rho_sp;                      // vapour spinodal density at T_in_eos (bracket)
+    // open ends: inlet pressure p0 (1 + p_amp sin(...)); its EOS at the inlet
+    // temperature T in e = in_e rho (b rho, CS: b rho / 4): in_A = R T / b (CS:
+    // 4 R T / b), in_B = a phi(T) / b^2 (CS: 16 a / b^2), in_rho = 1 / in_e; and
+    // the vapour spinodal density there (bracket)
+    double p0, p_amp, p_period, inv_p_period;
+    double in_e, in_rho, in_A, in_B, rho_sp;
     double dT_in;                       // inlet temperature - T_ref
     double dT_out;                      // held outlet temperature - T_ref (hold_out)
     int hold_out;                       // the outlet column holds its temperature

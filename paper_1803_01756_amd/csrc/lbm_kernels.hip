@@ -22,8 +22,8 @@
 // wave's own registers or, at its first and last row, through LDS with one
 // barrier per stage.
 //
-// What bounds it (us per step, FP32): on a small grid (128 x 32, 5.9) the
-// chain of stages of one workgroup, some 4 us, and the launch; on a middling
+// What bounds it (us per step, FP32): on a small grid (128 x 32, 5.5) the
+// chain of stages of one workgroup, some 3.5 us, and the launch; on a middling
 // one (2048 x 256, 15) that and the halo's arithmetic; on 8192 x 512 (85) the
 // memory traffic: the same tiles with the arithmetic taken out take 76, with
 // the loads and stores taken out 52, with either one alone 54 to 59.  A wave
@@ -501,40 +501,71 @@ struct RealOf<double> {
     using T = double;
 };
 
+// sin(2 pi n / period): the part of a turn past the nearest whole number of
+// periods (exact: one fma), folded to a quarter turn either way, and the
+// Taylor series there (up to x^21 / 21!; the next term is below 2e-18).  A
+// call of sin() took half a microsecond of the one wave that evaluates it, and
+// the whole workgroup waits for that wave.
+__device__ double sin_of_period(long long n, double period, double inv_period) {
+    const double t = (double)n;
+    double a = __builtin_fma(-__builtin_rint(t * inv_period), period, t) * inv_period;
+    if (fabs(a) > 0.25) a = copysign(0.5, a) - a;
+    const double x = a * 6.283185307179586, z = x * x;
+    double p = 1.0 / 51090942171709440000.0;
+    p = __builtin_fma(p, z, -1.0 / 121645100408832000.0);
+    p = __builtin_fma(p, z, 1.0 / 355687428096000.0);
+    p = __builtin_fma(p, z, -1.0 / 1307674368000.0);
+    p = __builtin_fma(p, z, 1.0 / 6227020800.0);
+    p = __builtin_fma(p, z, -1.0 / 39916800.0);
+    p = __builtin_fma(p, z, 1.0 / 362880.0);
+    p = __builtin_fma(p, z, -1.0 / 5040.0);
+    p = __builtin_fma(p, z, 1.0 / 120.0);
+    p = __builtin_fma(p, z, -1.0 / 6.0);
+    return __builtin_fma(p * z, x, x);
+}
+
 // Open ends: the inlet density at time level n, the vapour-branch root of
 // P_EOS(rho, T_in) = p0 (1 + p_amp sin(2 pi n / p_period)) (constant
-// p0 (1 + p_amp) when p_period <= 0).  Safeguarded Newton from rho_v inside
-// (0, rho_sp), rho_sp the vapour spinodal; every lane takes the same number
-// of iterations (5 to 8), so a channel gets the same bits alone and in a batch.
-// 60 fixed iterations took some 9 us of the step's critical path (1600 x 48).
+// p0 (1 + p_amp) when p_period <= 0).  Cleared of its denominators the
+// equation is a polynomial in e = b rho (RK: (1 - e) D; CS: e = b rho / 4,
+// (1 - e)^3) whose sign is that of P - target.  Safeguarded Newton from rho_v
+// inside (0, rho_sp), rho_sp the vapour spinodal; a step below 1e-9 of e is the
+// last (the next would be of its square).  Every lane takes the same number of
+// iterations (4 to 6), so a channel gets the same bits alone and in a batch.
+// It is the step's longest chain before the first barrier: with the quotients
+// and sin() it took 5 us of 15.7 (1600 x 48).
 __device__ double inlet_density(const Phys& k, long long n) {
-    const double T = k.T_in_eos;
-    const double target = k.p_period > 0.0
-        ? k.p0 * (1.0 + k.p_amp * sin(2.0 * 3.14159265358979323846 * (double)n / k.p_period))
+    const double p = k.p_period > 0.0
+        ? k.p0 * (1.0 + k.p_amp * sin_of_period(n, k.p_period, k.inv_p_period))
         : k.p0 * (1.0 + k.p_amp);
-    const bool cs = (k.flags & kEosCS) != 0;
-    const double s = 1.0 + k.kappa * (1.0 - sqrt(T * k.inv_Tc));
-    const double aphi = k.a * s * s;
-    double lo = 0.0, hi = k.rho_sp, r = k.rho_v;
-    for (int it = 0; it < 60; ++it) {
-        double P, dP;
-        if (cs) {
-            const double e = 0.25 * k.b * r, o = 1.0 - e, o3 = o * o * o;
-            P = r * k.R * T * (1.0 + e * (1.0 + e * (1.0 - e))) / o3 - k.a * r * r;
-            dP = k.R * T * (1.0 + e * (4.0 + e * (4.0 + e * (-4.0 + e)))) / (o3 * o) -
-                 2.0 * k.a * r;
-        } else {
-            const double br = k.b * r, omb = 1.0 - br, D = 1.0 + br * (2.0 - br);
-            P = r * k.R * T / omb - aphi * r * r / D;
-            dP = k.R * T / (omb * omb) - 2.0 * aphi * r * (1.0 + br) / (D * D);
-        }
-        if (P < target) lo = r; else hi = r;
-        double rn = r - (P - target) / dP;
-        if (fabs(rn - r) <= 4.5e-16 * r) return rn;  // at the root to rounding
-        if (!(rn > lo && rn < hi)) rn = 0.5 * (lo + hi);
-        r = rn;
+    const double A = k.in_A, B = k.in_B;
+    double c1, c2, c3, c4 = 0.0, c5 = 0.0;
+    if (k.flags & kEosCS) {
+        c1 = A + 3.0 * p;
+        c2 = A - B - 3.0 * p;
+        c3 = A + 3.0 * B + p;
+        c4 = -(A + 3.0 * B);
+        c5 = B;
+    } else {
+        c1 = A - p;
+        c2 = 2.0 * A - B + 3.0 * p;
+        c3 = B - A - p;
     }
-    return r;
+    double lo = 0.0, hi = k.rho_sp * k.in_e, e = k.rho_v * k.in_e;
+    for (int it = 0; it < 60; ++it) {
+        const double F = __builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(
+                             c5, e, c4), e, c3), e, c2), e, c1), e, -p);
+        const double dF = __builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(
+                              5.0 * c5, e, 4.0 * c4), e, 3.0 * c3), e, 2.0 * c2), e, c1);
+        if (F < 0.0) lo = e; else hi = e;
+        double y = __builtin_amdgcn_rcp(dF);
+        y = __builtin_fma(__builtin_fma(-dF, y, 1.0), y, y);
+        double en = __builtin_fma(-F, y, e);
+        if (fabs(en - e) <= 1e-9 * e) return en * k.in_rho;
+        if (!(en > lo && en < hi)) en = 0.5 * (lo + hi);
+        e = en;
+    }
+    return e * k.in_rho;
 }
 
 // Zou-He on an open end (zero transverse velocity, prescribed density), in
@@ -565,8 +596,7 @@ __device__ __forceinline__ void zou_he(R d[9], bool at_in, bool at_out, double r
 // Oscillating drive at time level n, evaluated on the device so that a channel
 // run alone and inside a batch sees the same bits.
 __device__ __forceinline__ double drive_at(const Phys& k, long long n) {
-    return k.period > 0.0 ? k.g_osc * sin(2.0 * 3.14159265358979323846 * (double)n / k.period)
-                          : 0.0;
+    return k.period > 0.0 ? k.g_osc * sin_of_period(n, k.period, k.inv_period) : 0.0;
 }
 
 // Add a wave's health word (see step_unit) to the counters: stat[0] gains
@@ -672,7 +702,18 @@ __device__ __forceinline__ void step_tile(const Grid& g, const Phys& k, const Bu
         if (at_out) p = v;
         return tri_of(v, m, p);
     };
-    const PhysR<R>& kr = pr<R>(k);
+    // The constants of the FP32 arithmetic.  Where a wave has registers to
+    // spare (one row each, the build with the optional features) they are
+    // kept in vector registers from the start: read from the kernel arguments
+    // where they are used, each group waits for the scalar cache in every
+    // stage of every wave (200 x 200: 9.4 us per step, so 8.2).  The plain build
+    // would lose its second workgroup per CU (1111 x 77: 10.5 and 13.1 us).
+    PhysR<R> kr = pr<R>(k);
+    if (kExt && kRows == 1 && sizeof(R) == 4) {
+        R* kv = reinterpret_cast<R*>(&kr);
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(kr) / sizeof(R)); ++i) asm("" : "+v"(kv[i]));
+    }
     const R T_ref = kr.T_ref, dTw = kr.dT_wall;
     const bool ramp = kExt && k.wall_ramp != 0;
     const R dTw_x = ramp ? (R)(k.dT_wall + (k.dT_w_end - k.dT_wall) * (double)cx / (double)(g.Nx - 1))
@@ -706,6 +747,8 @@ __device__ __forceinline__ void step_tile(const Grid& g, const Phys& k, const Bu
     const int yb = min(ya + g.seg_rows, g.y_first + g.rows);
     const int y0 = ya - kHalo + w * kRows;        // lattice row of the wave's row 0
     const int wS = max(w - 1, 0), wN = min(w + 1, kWaves - 1);
+    // waves past the upper halo end here (a barrier waits for running waves)
+    if (y0 >= yb + kHalo) return;
 
     // The wave's rows.  Rows past the tile's upper halo and plate rows are
     // not fluid; they load the first stored row (unused).
@@ -722,9 +765,10 @@ __device__ __forceinline__ void step_tile(const Grid& g, const Phys& k, const Bu
         rawlo[r] = kMX ? bload(rb, vlo, B.lo_in + (unsigned)rS.sr * rowb_lo, 0.0f) : 0.0f;
     }
     // the inlet density only where the strip holds the inlet column; the
-    // drive by the last wave alone, whose rows are mostly halo
+    // drive by the first wave alone, which starts first and whose rows are
+    // halo (by the last wave, 0.7 us later, everyone waited for it)
     const double rho_in = (open_x && __builtin_amdgcn_ballot_w64(at_in)) ? inlet_density(k, n) : 0.0;
-    if (w == kWaves - 1) L.drive = (R)drive_at(k, n);
+    if (w == 0) L.drive = (R)drive_at(k, n);
     // health of the owned nodes (the state at level n), in one register:
     // bits 0-30 count the Eq. 10 arguments clamped to psi = 0 (a lane owns
     // fewer than 2^20 rows), bit 31 is set once the lane has read a
@@ -989,9 +1033,27 @@ __device__ __forceinline__ bool tile_of_block(const Grid& g, int j, long long n,
     return strip < g.n_strips && seg >= 0 && seg < g.n_segs;
 }
 
+// Reads one word of every 64-byte line of the step's constants, so that the
+// lines come into the scalar cache together at the start: read where they are
+// needed, each costs a trip to memory in its turn, some 13 in all (0.2 to
+// 0.5 us of every launch).  A batch's slots do not fit that cache together,
+// and the same reads there cost 1.5 %.
+template <size_t kBytes>
+__device__ __forceinline__ void touch_kernarg() {
+    const auto* p =
+        (const __attribute__((address_space(4))) unsigned*)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr int n = (int)((kBytes + 63) / 64);
+    unsigned v[n];
+#pragma unroll
+    for (int i = 0; i < n; ++i) v[i] = p[16 * i];
+#pragma unroll
+    for (int i = 0; i < n; ++i) asm volatile("" ::"s"(v[i]));
+}
+
 template <class S, bool kMX, bool kExt, int kRows, int kWaves, int kPerSimd>
 __global__ __launch_bounds__(kLanes* kWaves) __attribute__((amdgpu_waves_per_eu(kPerSimd)))
 void step_kernel(Grid g, Phys k, Bufs<S> B, long long n) {
+    touch_kernarg<sizeof(Grid) + sizeof(Phys) + sizeof(Bufs<S>) + sizeof(n)>();
     __shared__ TileLds<typename RealOf<S>::T, kWaves, kExt> L;
     int strip, seg;
     if (!tile_of_block(g, blockIdx.x, n, strip, seg)) return;  // whole workgroups only

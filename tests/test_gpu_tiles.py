@@ -75,3 +75,29 @@ def test_optional_features_over_shapes(orc, which, precision):
     print(e, flush=True)
     tol = (1e-10, 1e-8, 1e-10) if precision == lbm.LBM_FP64 else (1e-5, 1e-5, 1e-5)
     assert e["rho"] < tol[0] and e["u"] < tol[1] and e["T"] < tol[2]
+
+
+@pytest.mark.parametrize("eos", ["rk", "cs"])
+@pytest.mark.parametrize("period", [7.0, 90.5, 1e6, 0.0])
+def test_inlet_density_is_the_root_of_its_pressure(eos, period):
+    """The density read at the inlet column has the pressure that level n
+    prescribes: P(rho, T_in) = p0 (1 + p_amp sin(2 pi n / period)), to the
+    rounding of a root whose pressure is known to some 1e-15 (times the
+    condition of P near the vapour spinodal, below 1e3)."""
+    print("\n[case] inlet %s period=%g" % (eos, period), flush=True)
+    if eos == "rk":
+        p = configs.open_channel(61, 20, p_period=period, precision=lbm.LBM_FP64)
+    else:
+        p = configs.channel_params_cs(61, 20, precision=lbm.LBM_FP64, g_osc=0.0, period=0.0,
+                                      flags=lbm.LBM_OPEN_X, p_amp=0.05, p_period=period)
+    p = lbm.lbm_params_resolve(p)
+    T_in = p.T_in if p.T_in > 0.0 else p.T_0
+    p0 = lbm.lbm_eos_pressure(p, p.rho_v, T_in)[0]
+    s = lbm.Sim(p, configs.initial_density(p, 1))
+    for n in (0, 1, 2, 5, 23):
+        s.step(n - s.n)
+        rho = s.moments()[0][2:-2, 0]
+        want = p0 * (1.0 + p.p_amp * (np.sin(2.0 * np.pi * n / period) if period > 0.0 else 1.0))
+        for r in rho:
+            assert abs(lbm.lbm_eos_pressure(p, r, T_in)[0] / want - 1.0) < 1e-12
+    s.close()

@@ -559,7 +559,7 @@ def main():
                     help="skip the secondary precisions and the cache-resident size")
     ap.add_argument("--no-tune", action="store_true")
     ap.add_argument("--seg-rows", type=int, default=0,
-                    help="force the launch shape (rows per wave) instead of autotuning")
+                    help="force the launch shape (rows of a segment) instead of autotuning")
     ap.add_argument("--no-batch", action="store_true", help="skip the batched and served runs")
     ap.add_argument("--batch-steps", type=int, default=10000)
     ap.add_argument("--serve-requests", type=int, default=1000,

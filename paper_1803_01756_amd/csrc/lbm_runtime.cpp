@@ -507,7 +507,7 @@ int default_tile(const lbm_params& p, int rows) {
     };
     // While a grid is a few workgroups per CU, the time of a step is one
     // workgroup's way through the stages, and the flattest tile (one row per
-    // wave) is the shortest: 128 x 32 in 5.9 us against 7.4 (Mid) and 8.6
+    // wave) is the shortest: 128 x 32 (six rows) in 5.9 us against 7.4 (Mid) and 8.6
     // (Tall), 1024 x 128 (399 flat tiles) 8.4 / 8.5 / 9.8.  Beyond that its 10
     // halo rows per 6 of its own fill the chip (2048 x 256: 20.7 / 14.1 /
     // 15.2).  From some four rounds of Tall tiles (two per CU) on, their fewer

@@ -384,7 +384,7 @@ class Sim:
         lbm_load(self.h, blob)
 
     def set_launch(self, seg_rows: int):
-        """Rows per wave of the step kernel; <= 0 restores the default
+        """Rows of a segment of the step; <= 0 restores the default
         (lbm_set_launch).  Results do not depend on it."""
         lbm_set_launch(self.h, seg_rows)
 
@@ -489,7 +489,7 @@ class Pool:
         return int(lib().lbm_pool_slot_time(C.c_void_p(self.h), int(slot)))
 
     def set_launch(self, seg_rows: int):
-        """Rows per wave for every slot; <= 0: per-slot default."""
+        """Rows of a segment for every slot; <= 0: per-slot default."""
         _check(lib().lbm_pool_set_launch(C.c_void_p(self.h), int(seg_rows)))
 
     def autotune(self, steps_per_trial: int = 10) -> float:
@@ -500,7 +500,7 @@ class Pool:
         return ms.value
 
     def slot_launch(self, slot: int):
-        """(rows per wave, waves per step) of a slot."""
+        """(rows of a segment, tiles per step) of a slot."""
         sr, w = C.c_int32(), C.c_int32()
         _check(lib().lbm_pool_slot_launch(C.c_void_p(self.h), int(slot), C.byref(sr),
                                           C.byref(w)))

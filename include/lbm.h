@@ -305,9 +305,9 @@ lbm_status lbm_load(lbm_sim* sim, const void* host, size_t bytes);
 
 /* Launch shape of the fused step kernel: the grid is cut into strips of 54
  * columns and segments of seg_rows fluid rows; a workgroup takes a segment, or
- * an even share of one taller than the tallest tile (26 rows).  seg_rows <= 0
+ * an even share of one taller than the tallest tile (26 rows, mass-exact 30).  seg_rows <= 0
  * restores the default: tiles of up to 6 rows on a small grid (a few per CU),
- * 14 on a middling and 26 on a large one (FP64: 6, 22 and 26).  lbm_autotune
+ * 14 on a middling and 26 on a large one (mass-exact 30; FP64: 6, 22 and 26).  lbm_autotune
  * times candidate shapes instead.  lbm_get_launch reports seg_rows and the
  * number of segments.  The result of a step does not depend on the shape
  * (bitwise). */

@@ -23,13 +23,16 @@ constexpr int kOwned = kLanes - 2 * kHalo;
 // does not fit beside the first (8192 x 512: 118 and 112 us for 96 with 8).
 // FP32: Mid keeps three workgroups on a CU, Tall two; taller waves of five
 // rows (5 x 8) leave four waves per SIMD and measured 87.3 against Tall's 84.3.
+// Mass-exact storage keeps one FP64 density per row more: in Tall's 80
+// registers it spills three and writes 31 MB of them per step (8192 x 512: 104
+// us), so its tall tile is the 5 x 8 one (97.5; 4 x 8: 100.8).
 // FP64: the halo exchange in LDS leaves one workgroup per CU.
 struct TileShape {
     int rows, waves, per_simd;
     constexpr int own() const { return rows * waves - 2 * kHalo; }
 };
-enum { kTileFlat, kTileMid, kTileTall, kTileFlat64, kTileMid64, kTileTall64, kTileCount };
-constexpr TileShape kTiles[kTileCount] = {{1, 16, 4}, {3, 8, 6},  {3, 12, 6},   // FP32
+enum { kTileFlat, kTileMid, kTileTall, kTileTallMX, kTileFlat64, kTileMid64, kTileTall64, kTileCount };
+constexpr TileShape kTiles[kTileCount] = {{1, 16, 4}, {3, 8, 6},  {3, 12, 6}, {5, 8, 4},  // FP32
                                           {1, 16, 4}, {2, 16, 4}, {3, 12, 3}};  // FP64
 
 // Constants that enter arithmetic done in the storage precision R, given in

@@ -1516,7 +1516,8 @@ static hipError_t step_impl(const Grid& g, const Phys& k, const Bufs<S>& b, int6
     } else {
         if (g.tile == kTileFlat) return launch_tile<S, kMX, kExt, kTileFlat>(g, k, b, n, s);
         if (g.tile == kTileMid) return launch_tile<S, kMX, kExt, kTileMid>(g, k, b, n, s);
-        if (g.tile == kTileTall) return launch_tile<S, kMX, kExt, kTileTall>(g, k, b, n, s);
+        constexpr int tall = kMX ? kTileTallMX : kTileTall;
+        if (g.tile == tall) return launch_tile<S, kMX, kExt, tall>(g, k, b, n, s);
     }
     return hipErrorInvalidValue;
 }

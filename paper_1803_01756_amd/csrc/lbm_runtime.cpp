@@ -520,7 +520,8 @@ int default_tile(const lbm_params& p, int rows) {
         return tiles(lbmk::kTileTall64) <= 1024 ? lbmk::kTileMid64 : lbmk::kTileTall64;
     }
     if (tiles(lbmk::kTileFlat) <= 512) return lbmk::kTileFlat;
-    return tiles(lbmk::kTileTall) <= kTallTiles ? lbmk::kTileMid : lbmk::kTileTall;
+    if (tiles(lbmk::kTileTall) <= kTallTiles) return lbmk::kTileMid;
+    return p.precision == LBM_FP32_DEV_MASSEXACT ? lbmk::kTileTallMX : lbmk::kTileTall;
 }
 
 int default_rows(const lbm_params& p, int rows, int tile) {
@@ -533,9 +534,12 @@ int default_rows(const lbm_params& p, int rows, int tile) {
 }
 
 int tile_for(const lbm_params& p, int seg_rows) {
-    int t = p.precision == LBM_FP64 ? lbmk::kTileFlat64 : lbmk::kTileFlat;
-    for (int i = 0; i < 2 && lbmk::kTiles[t].own() < seg_rows; ++i) ++t;
-    return t;
+    const int flat = p.precision == LBM_FP64 ? lbmk::kTileFlat64 : lbmk::kTileFlat;
+    const int tall = p.precision == LBM_FP64                 ? lbmk::kTileTall64
+                     : p.precision == LBM_FP32_DEV_MASSEXACT ? lbmk::kTileTallMX
+                                                             : lbmk::kTileTall;
+    if (seg_rows <= lbmk::kTiles[flat].own()) return flat;
+    return seg_rows <= lbmk::kTiles[flat + 1].own() ? flat + 1 : tall;
 }
 
 void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, int tile, Grid& g) {

@@ -101,3 +101,11 @@ def test_inlet_density_is_the_root_of_its_pressure(eos, period):
         for r in rho:
             assert abs(lbm.lbm_eos_pressure(p, r, T_in)[0] / want - 1.0) < 1e-12
     s.close()
+
+
+@pytest.mark.parametrize("precision", STORAGES)
+def test_heights_around_the_tallest_tiles(precision):
+    print("\n[case] tall tiles precision=%d" % precision, flush=True)
+    p = configs.channel_params(120, 95, 110.0, 0.8, 2e-6, 300.0, precision, 0, g_y=-1e-5)
+    rho0 = inputs.density_field(120, 95, p.rho_v, 0.01, 3)
+    _same(p, rho0, 6, (22, 23, 26, 27, 29, 30, 31, 93))

@@ -686,7 +686,7 @@ lbm_status lbm_pool_autotune(lbm_pool* P, int32_t steps_per_trial, double* best_
               s.p.T_w_end > 0.0 || s.p.alpha_max > 0.0;
         present[row_bucket(s.L.rows)] = 1;
     }
-    const int dflt = default_target(P, act);
+    const int dflt = P->default_target = default_target(P, act);
     // time one policy (segment-height target per bucket) over the copies
     int trial_steps = steps_per_trial;
     auto trial = [&](const int* target, double* ms_out) -> hipError_t {

@@ -73,7 +73,8 @@ int default_rows(const lbm_params& p, int rows, int tile);
 int tile_for(const lbm_params& p, int seg_rows);
 // Grid of a launch with segments of seg_rows rows in tiles of shape `tile`:
 // segments taller than a tile are split evenly.
-void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, int tile, lbmk::Grid& g);
+void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, int tile, lbmk::Grid& g,
+               bool in_batch = false);
 // Segments of about `target` rows, balanced over the channel's rows.
 int balanced_rows(int rows, int target);
 void fill_phys(const lbm_params& p, lbmk::Phys& k);

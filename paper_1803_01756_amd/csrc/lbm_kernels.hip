@@ -1016,7 +1016,7 @@ __device__ __forceinline__ void step_tile(const Grid& g, const Phys& k, const Bu
 // time, so that the tiles in flight on an XCD are a compact patch whose halos
 // meet in its L2, and all XCDs are on the same rows (HBM reads per step on
 // 8192 x 512: 176 MB against 235 for one row band per XCD, 88.9 us against
-// 93.9).  Steps alternate between walking the rows up and down: the rows a
+// 93.9; fill_grid has the line).  Steps alternate between walking the rows up and down: the rows a
 // step wrote last are then read first, while the memory-side cache still has
 // them (84.8 against 88.4 us).  A narrow grid gives every XCD a run of tiles in
 // row order, for the same shared halos (against tiles dealt one by one: 100 x 300

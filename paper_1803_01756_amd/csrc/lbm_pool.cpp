@@ -349,7 +349,7 @@ lbm_status lbm_pool_admit(lbm_pool* P, const lbm_params* pin, const double* rho0
     }
     lbmhost::fill_phys(p, s.k);
     s.seg_rows = seg_rows_for(P, s);
-    lbmhost::fill_grid(p, L, s.seg_rows, lbmhost::tile_for(p, s.seg_rows), s.g);
+    lbmhost::fill_grid(p, L, s.seg_rows, lbmhost::tile_for(p, s.seg_rows), s.g, true);
     s.steps_left = nsteps;
     s.used = true;
     P->used += need;
@@ -426,7 +426,7 @@ lbm_status lbm_pool_run(lbm_pool* P, int32_t chunk) {
         }
         const int take = (int)std::min<int64_t>(chunk, s.steps_left);
         lbmk::Slot& t = tab[j];
-        lbmhost::fill_grid(s.p, s.L, s.seg_rows, tile, t.g);
+        lbmhost::fill_grid(s.p, s.L, s.seg_rows, tile, t.g, true);
         t.k = s.k;
         t.mem = s.mem;
         for (int q = 0; q < 2; ++q) {
@@ -701,7 +701,7 @@ lbm_status lbm_pool_autotune(lbm_pool* P, int32_t steps_per_trial, double* best_
             const SlotState& s = P->slots[act[j]];
             lbmk::Slot& q = tab[j];
             q.k = s.k;
-            lbmhost::fill_grid(s.p, s.L, height(s), tile, q.g);
+            lbmhost::fill_grid(s.p, s.L, height(s), tile, q.g, true);
             q.mem = shadow + at[j];
             for (int c = 0; c < 2; ++c) {
                 q.off_f[c] = (unsigned)(reinterpret_cast<char*>(s.f[c]) - s.mem);

@@ -542,7 +542,8 @@ int tile_for(const lbm_params& p, int seg_rows) {
     return seg_rows <= lbmk::kTiles[flat + 1].own() ? flat + 1 : tall;
 }
 
-void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, int tile, Grid& g) {
+void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, int tile, Grid& g,
+               bool in_batch) {
     g.Nx = p.Nx;
     g.Ny = p.Ny;
     g.pitch = L.pitch;
@@ -558,7 +559,12 @@ void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, int tile, Gri
     g.n_strips = strips_of(p);
     g.n_segs = (g.rows + g.seg_rows - 1) / g.seg_rows;
     // chunks of strips per XCD only where the last one is not left nearly idle
-    g.strips_per_xcd = g.n_strips >= 32 ? (g.n_strips + 7) / 8 : 0;
+    // Chunks of columns for the XCDs from four strips each on: with runs of
+    // tiles instead 2048 x 256 (38 strips) takes 15.8 us for 15.3, 3400 x 512
+    // (63) 37.1 for 33.1.  In a batch every slot takes runs: chunks leave the
+    // XCDs of a slot with unequal work (a pool of 20 channels 76.1 us for
+    // 73.4, 64 channels 45.4 GLUPS for 46.5).
+    g.strips_per_xcd = !in_batch && g.n_strips >= 32 ? (g.n_strips + 7) / 8 : 0;
     g.n_blocks = g.strips_per_xcd ? 8 * g.strips_per_xcd * g.n_segs
                                   : (g.n_strips * g.n_segs + 7) / 8 * 8;
 }

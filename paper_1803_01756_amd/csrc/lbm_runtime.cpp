@@ -520,7 +520,15 @@ int default_tile(const lbm_params& p, int rows) {
         return tiles(lbmk::kTileTall64) <= 1024 ? lbmk::kTileMid64 : lbmk::kTileTall64;
     }
     if (tiles(lbmk::kTileFlat) <= 512) return lbmk::kTileFlat;
-    if (tiles(lbmk::kTileTall) <= kTallTiles) return lbmk::kTileMid;
+    // The FP32 build with the optional features fits two Mid workgroups or one
+    // Tall one on a CU, and Tall wins earlier: with gravity and mixed plates
+    // 4096 x 256 (760 tall tiles) in 31.6 (Mid) against 31.9, 3000 x 512 (1120)
+    // 44.3 / 42.0, 4096 x 512 55.8 / 52.8.
+    const bool ext = (p.flags & (LBM_FRAME_T | LBM_FRAME_RHO | LBM_EOS_CS | LBM_OPEN_X |
+                                 LBM_PHASE_PROPS | LBM_TOP_MIXED)) ||
+                     p.T_w_end > 0.0 || p.alpha_max > 0.0;
+    const long long tall_from = ext && p.precision == LBM_FP32_DEV ? 1024 : kTallTiles;
+    if (tiles(lbmk::kTileTall) <= tall_from) return lbmk::kTileMid;
     return p.precision == LBM_FP32_DEV_MASSEXACT ? lbmk::kTileTallMX : lbmk::kTileTall;
 }
 

@@ -25,8 +25,10 @@ namespace {
 #define PCHK(expr)                                                                        \
     do {                                                                                  \
         hipError_t e_ = (expr);                                                           \
-        if (e_ != hipSuccess)                                                             \
+        if (e_ != hipSuccess) {                                                           \
+            (void)hipGetLastError(); /* or the next launch would report it again */       \
             return fail(LBM_EDEVICE, "%s failed: %s", #expr, hipGetErrorString(e_));      \
+        }                                                                                 \
     } while (0)
 
 struct SlotState {
@@ -139,11 +141,15 @@ lbm_status ensure_table(lbm_pool* P, int n) {
     return LBM_OK;
 }
 
+// Moment arrays for `cells` nodes.  The old ones go first, so that both need
+// not fit together; if the new ones do not fit either the pool holds none, and
+// the next read-out or admission asks for its own.
 lbm_status ensure_mom(lbm_pool* P, size_t cells) {
     if (cells <= P->mom_cells) return LBM_OK;
     PCHK(hipStreamSynchronize(P->aux));
     if (P->mom) PCHK(hipFree(P->mom));
     P->mom = nullptr;
+    P->mom_cells = 0;
     PCHK(hipMalloc(reinterpret_cast<void**>(&P->mom), cells * 4 * sizeof(double)));
     P->mom_cells = cells;
     return LBM_OK;
@@ -189,6 +195,7 @@ lbm_status ensure_stat(lbm_pool* P, int n) {
         e = hipMemcpy(d, P->stat_dev, (size_t)P->stat_cap * kSlotStat * sizeof(*d),
                       hipMemcpyDeviceToDevice);
     if (e != hipSuccess) {
+        (void)hipGetLastError();
         (void)hipFree(d);
         if (h) (void)hipHostFree(h);
         return fail(LBM_EDEVICE, "health counters: %s", hipGetErrorString(e));
@@ -523,6 +530,8 @@ lbm_status lbm_pool_moments(lbm_pool* P, int32_t id, double* rho, double* ux, do
     PCHK(hipStreamWaitEvent(P->aux, s->ready, 0));
     PCHK(hipStreamWaitEvent(P->aux, s->done, 0));
     const size_t cells = (size_t)s->p.Nx * s->p.Ny;
+    const lbm_status st = ensure_mom(P, cells);
+    if (st != LBM_OK) return st;
     double* const outs[4] = {rho, ux, uy, T};
     double* const dev[4] = {P->mom, P->mom + cells, P->mom + 2 * cells, P->mom + 3 * cells};
     const lbmhost::ReadoutPlan plan = lbmhost::plan_readout(outs, dev, cells);

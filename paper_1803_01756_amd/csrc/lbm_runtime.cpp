@@ -423,11 +423,11 @@ namespace lbmhost {
 hipError_t reserve_readout(ReadoutMem& m, int Nx, int Ny) {
     if (lbmk::readout_blocks(Nx, Ny) <= m.cap) return hipSuccess;
     const int n = std::max(lbmk::readout_blocks(Nx, Ny), 2 * m.cap);
-    free_readout(m);
     void* p = nullptr;
     const hipError_t e = hipHostMalloc(&p, kStatWords * sizeof(unsigned long long) +
                                                n * sizeof(unsigned), hipHostMallocDefault);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) return e;  // what m holds stays
+    free_readout(m);
     m.ro.words = static_cast<unsigned long long*>(p);
     m.ro.bad = reinterpret_cast<unsigned*>(m.ro.words + kStatWords);
     m.cap = n;

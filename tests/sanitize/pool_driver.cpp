@@ -1,0 +1,255 @@
+/* The slot pool's host code on a HIP runtime made of host memory, with every
+ * allocation of an admission failing in turn.
+ *
+ * The HIP calls that lbm_runtime.cpp and lbm_pool.cpp make are defined here:
+ * device and pinned memory come from malloc and are kept in a table, copies
+ * check that their device side lies in it, work happens at once.  The kernel
+ * launches check their pointers against the table and write what the host
+ * reads back.  One chosen allocation (hipMalloc or hipHostMalloc) fails with
+ * hipErrorOutOfMemory; as on a GPU that error stays the thread's last error
+ * until hipGetLastError takes it, which every launch here ends with.
+ *
+ * Test infrastructure: tests/test_pool_allocation.py compiles this with both
+ * sources and the sanitizers and runs it on the CPU. */
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "lbm.h"
+#include "lbm_internal.h"
+
+static int failures = 0;
+static std::string where;
+#define EXPECT(cond)                                                                         \
+    do {                                                                                     \
+        if (!(cond)) {                                                                       \
+            fprintf(stderr, "%d [%s]: expectation failed: %s (%s)\n", __LINE__, where.c_str(), #cond, \
+                    lbm_last_error());                                                       \
+            ++failures;                                                                      \
+        }                                                                                    \
+    } while (0)
+
+/* ---- the runtime ------------------------------------------------------------ */
+struct Block {
+    size_t bytes;
+    bool host;
+};
+static std::map<char*, Block> blocks;
+static long allocs = 0, fail_at = -1;
+static hipError_t last = hipSuccess;
+
+static const std::pair<char* const, Block>* find(const void* p) {
+    auto it = blocks.upper_bound((char*)p);
+    if (it == blocks.begin()) return nullptr;
+    --it;
+    return (char*)p < it->first + it->second.bytes ? &*it : nullptr;
+}
+static bool holds(const void* p, size_t bytes) {
+    const auto* b = find(p);
+    return b && (size_t)((char*)p - b->first) + bytes <= b->second.bytes;
+}
+static hipError_t result(hipError_t e) {
+    if (e != hipSuccess) last = e;
+    return e;
+}
+static hipError_t take(void** out, size_t bytes, bool host) {
+    if (allocs++ == fail_at) return result(hipErrorOutOfMemory);
+    char* p = (char*)malloc(bytes);
+    blocks[p] = {bytes, host};
+    *out = p;
+    return hipSuccess;
+}
+static hipError_t give(void* p, bool host) {
+    if (!p) return hipSuccess;
+    auto it = blocks.find((char*)p);
+    EXPECT(it != blocks.end() && it->second.host == host);
+    if (it == blocks.end()) return result(hipErrorInvalidValue);
+    free(it->first);
+    blocks.erase(it);
+    return hipSuccess;
+}
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) { return take(p, n, false); }
+hipError_t hipFree(void* p) { return give(p, false); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return take(p, n, true); }
+hipError_t hipHostFree(void* p) { return give(p, true); }
+hipError_t hipGetLastError() {
+    const hipError_t e = last;
+    last = hipSuccess;
+    return e;
+}
+const char* hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }
+hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipStreamCreate(hipStream_t* s) { return *s = (hipStream_t)1, hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { return *e = (hipEvent_t)1, hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return *e = (hipEvent_t)1, hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }
+hipError_t hipMemset(void* p, int v, size_t n) {
+    EXPECT(holds(p, n));
+    if (holds(p, n)) memset(p, v, n);
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* p, int v, size_t n, hipStream_t) { return hipMemset(p, v, n); }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind kind) {
+    const bool ok = (kind == hipMemcpyDeviceToHost || holds(d, n)) &&
+                    (kind == hipMemcpyHostToDevice || holds(s, n));
+    EXPECT(ok);
+    if (ok) memmove(d, s, n);
+    return ok ? hipSuccess : result(hipErrorInvalidValue);
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind kind, hipStream_t) {
+    return hipMemcpy(d, s, n, kind);
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+    const auto* b = find(p);
+    if (!b) return result(hipErrorInvalidValue);
+    memset(a, 0, sizeof(*a));
+    a->type = b->second.host ? hipMemoryTypeHost : hipMemoryTypeDevice;
+    a->devicePointer = const_cast<void*>(p);
+    return hipSuccess;
+}
+hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* size, hipDeviceptr_t p) {
+    const auto* b = find(p);
+    if (!b) return result(hipErrorInvalidValue);
+    *base = b->first;
+    *size = b->second.bytes;
+    return hipSuccess;
+}
+}  // extern "C"
+
+/* ---- the kernel launches ------------------------------------------------------ */
+namespace lbmk {
+int readout_blocks(int Nx, int Ny) { return ((Nx + 63) / 64) * ((Ny + 7) / 8); }
+
+hipError_t launch_moments_f32(const Grid& g, const Phys&, const float* f, const float*, const float* T,
+                              const Moments& out, int64_t, const unsigned long long* stat,
+                              const Readout& ro, hipStream_t) {
+    const size_t bytes = (size_t)g.Nx * g.Ny * sizeof(double);
+    const int nb = readout_blocks(g.Nx, g.Ny);
+    const bool ok = holds(f, 9 * (size_t)g.plane * 4) && holds(T, (size_t)g.plane * 4) &&
+                    holds(stat, kStepWords * 8) && holds(ro.words, kStepWords * 8) &&
+                    holds(ro.bad, nb * sizeof(unsigned));
+    EXPECT(ok);
+    if (!ok) return hipGetLastError();
+    double* const to[4] = {out.rho, out.ux, out.uy, out.T};
+    for (int q = 0; q < 4; ++q) {
+        if (!to[q]) continue;
+        EXPECT(holds(to[q], bytes));
+        if (holds(to[q], bytes))
+            for (int i = 0; i < g.Nx * g.Ny; ++i) to[q][i] = 10.0 * g.Nx + q;
+    }
+    memcpy(ro.words, stat, kStepWords * 8);
+    memset(ro.bad, 0, nb * sizeof(unsigned));
+    return hipGetLastError();
+}
+hipError_t launch_init_f32(const Grid& g, const Phys&, const double* rho0, float* f, float*, float* T,
+                           hipStream_t) {
+    EXPECT(holds(rho0, (size_t)g.Nx * g.Ny * sizeof(double)));
+    EXPECT(holds(f, 9 * (size_t)g.plane * 4) && holds(T, (size_t)g.plane * 4));
+    return hipGetLastError();
+}
+hipError_t launch_step_batched(const Slot* slots, int n, int, int, int, bool, hipStream_t) {
+    EXPECT(holds(slots, n * sizeof(Slot)));
+    return hipGetLastError();
+}
+/* not reached by a pool */
+hipError_t launch_init_f64(const Grid&, const Phys&, const double*, double*, double*, hipStream_t) { abort(); }
+hipError_t launch_moments_f64(const Grid&, const Phys&, const double*, const double*, const Moments&, int64_t,
+                              const unsigned long long*, const Readout&, hipStream_t) { abort(); }
+hipError_t launch_step_f32(const Grid&, const Phys&, const Bufs<float>&, bool, int64_t, hipStream_t) { abort(); }
+hipError_t launch_step_f64(const Grid&, const Phys&, const Bufs<double>&, int64_t, hipStream_t) { abort(); }
+hipError_t launch_reduce(const double*, const double*, const double*, const double*, int, double, double*,
+                         double*, hipStream_t) { abort(); }
+hipError_t launch_reduce_state_f32(const Grid&, const Phys&, const float*, const float*, const float*, double,
+                                   int64_t, double*, hipStream_t) { abort(); }
+hipError_t launch_reduce_state_f64(const Grid&, const Phys&, const double*, const double*, double, int64_t,
+                                   double*, hipStream_t) { abort(); }
+hipError_t launch_copy(const void*, void*, size_t, hipStream_t) { abort(); }
+}  // namespace lbmk
+
+/* ---- the checks ------------------------------------------------------------------ */
+static lbm_params channel(int Nx, int Ny) {
+    lbm_params p;
+    lbm_params_default(&p);
+    p.Nx = Nx;
+    p.Ny = Ny;
+    EXPECT(lbm_params_resolve(&p) == LBM_OK);
+    return p;
+}
+
+static void read_out(lbm_pool* P, int slot, const lbm_params& p) {
+    std::vector<double> a[4];
+    for (auto& v : a) v.assign((size_t)p.Nx * p.Ny, -1.0);
+    EXPECT(lbm_pool_moments(P, slot, a[0].data(), a[1].data(), a[2].data(), a[3].data()) == LBM_OK);
+    for (int q = 0; q < 4; ++q) EXPECT(a[q].front() == 10.0 * p.Nx + q && a[q].back() == 10.0 * p.Nx + q);
+}
+
+/* A small slot lives while a larger one is admitted and the k-th allocation
+ * of that admission fails: the admission reports it, and the small slot, a
+ * second larger one and one in between are read out as if nothing had been. */
+static bool admission(int k) {
+    where = "admission " + std::to_string(k);
+    const lbm_params small = channel(64, 20), large = channel(300, 90), mid = channel(130, 60);
+    lbm_pool* P = nullptr;
+    int32_t a = -1, b = -1, c = -1;
+    EXPECT(lbm_pool_create((size_t)1 << 30, nullptr, &P) == LBM_OK);
+    EXPECT(lbm_pool_admit(P, &small, nullptr, 10, &a) == LBM_OK);
+    fail_at = allocs + k;
+    const lbm_status st = lbm_pool_admit(P, &large, nullptr, 10, &b);
+    const bool failed = allocs > fail_at;
+    fail_at = -1;
+    EXPECT(failed || st == LBM_OK);
+    read_out(P, a, small);
+    EXPECT(lbm_pool_admit(P, &mid, nullptr, 10, &c) == LBM_OK);
+    read_out(P, c, mid);
+    if (b >= 0) read_out(P, b, large);
+    EXPECT(lbm_pool_admit(P, &large, nullptr, 10, &b) == LBM_OK);
+    read_out(P, b, large);
+    EXPECT(lbm_pool_run(P, 10) == LBM_OK);
+    read_out(P, a, small);
+    EXPECT(lbm_pool_destroy(P) == LBM_OK);
+    EXPECT(blocks.empty());
+    return failed;
+}
+
+/* The same for a pool's first admission. */
+static bool first(int k) {
+    where = "first " + std::to_string(k);
+    const lbm_params p = channel(64, 20);
+    lbm_pool* P = nullptr;
+    int32_t a = -1;
+    EXPECT(lbm_pool_create((size_t)1 << 30, nullptr, &P) == LBM_OK);
+    fail_at = allocs + k;
+    const lbm_status st = lbm_pool_admit(P, &p, nullptr, 10, &a);
+    const bool failed = allocs > fail_at;
+    fail_at = -1;
+    EXPECT((st != LBM_OK) == failed && (a < 0) == failed);
+    if (failed) EXPECT(lbm_pool_admit(P, &p, nullptr, 10, &a) == LBM_OK);
+    EXPECT(lbm_pool_run(P, 10) == LBM_OK);
+    read_out(P, a, p);
+    EXPECT(lbm_pool_destroy(P) == LBM_OK);
+    EXPECT(blocks.empty());
+    return failed;
+}
+
+int main(int argc, char** argv) {
+    const std::string what = argc > 1 ? argv[1] : "admission";
+    int k = 0;
+    while ((what == "first" ? first(k) : admission(k)) && k < 100) ++k;
+    printf("%s: %d allocations failed in turn, %d failed expectations\n", what.c_str(), k, failures);
+    return failures || k == 0;
+}

@@ -1,0 +1,40 @@
+"""The pool's host code when an allocation fails (CPU only).
+
+tests/sanitize/pool_driver.cpp is a HIP runtime made of host memory and the
+library's host sources compiled with it under AddressSanitizer and
+UndefinedBehaviorSanitizer: every allocation that an admission makes fails in
+turn, and the slots admitted before it must still be stepped and read out
+through valid memory."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_1803_01756_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    exe = str(tmp_path_factory.mktemp("pool") / "pool_driver")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
+                        "-fno-sanitize-recover=all", "-D__HIP_PLATFORM_AMD__", "-w",
+                        "-I", os.path.join(rocm, "include"), "-I", os.path.join(ROOT, "include"),
+                        "-I", CSRC, "-o", exe, os.path.join(HERE, "sanitize", "pool_driver.cpp"),
+                        os.path.join(CSRC, "lbm_runtime.cpp"), os.path.join(CSRC, "lbm_pool.cpp")],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+    return exe
+
+
+@pytest.mark.parametrize("what", ["first", "admission"])
+def test_failed_allocation_leaves_the_pool_usable(driver, what):
+    r = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True,
+                       timeout=300)
+    print(r.stdout)
+    assert r.returncode == 0 and "0 failed expectations" in r.stdout, r.stdout

@@ -126,13 +126,14 @@ namespace {
 lbm_status ensure_table(lbm_pool* P, int n) {
     if (n <= P->table_cap) return LBM_OK;
     PCHK(hipStreamSynchronize(P->main));
+    const int cap = std::max(n, 2 * P->table_cap);
+    P->table_cap = 0;  // until all three parts are there
     for (int b = 0; b < 2; ++b) {
         if (P->table_host[b]) PCHK(hipHostFree(P->table_host[b]));
         P->table_host[b] = nullptr;
     }
     if (P->table_dev) PCHK(hipFree(P->table_dev));
     P->table_dev = nullptr;
-    const int cap = std::max(n, 2 * P->table_cap);
     PCHK(hipMalloc(reinterpret_cast<void**>(&P->table_dev), cap * sizeof(lbmk::Slot)));
     for (int b = 0; b < 2; ++b)
         PCHK(hipHostMalloc(reinterpret_cast<void**>(&P->table_host[b]), cap * sizeof(lbmk::Slot),

@@ -1,5 +1,5 @@
 /* The slot pool's host code on a HIP runtime made of host memory, with every
- * allocation of an admission failing in turn.
+ * allocation of an admission or a run failing in turn.
  *
  * The HIP calls that lbm_runtime.cpp and lbm_pool.cpp make are defined here:
  * device and pinned memory come from malloc and are kept in a table, copies
@@ -246,10 +246,35 @@ static bool first(int k) {
     return failed;
 }
 
+/* The same for the batch's table, which a run of more slots makes larger: a
+ * run of fewer slots then goes on as before. */
+static bool run_growth(int k) {
+    where = "run " + std::to_string(k);
+    const lbm_params p = channel(64, 20);
+    lbm_pool* P = nullptr;
+    int32_t id[3];
+    EXPECT(lbm_pool_create((size_t)1 << 30, nullptr, &P) == LBM_OK);
+    EXPECT(lbm_pool_admit(P, &p, nullptr, 100, &id[0]) == LBM_OK);
+    EXPECT(lbm_pool_run(P, 10) == LBM_OK);
+    for (int i = 1; i < 3; ++i) EXPECT(lbm_pool_admit(P, &p, nullptr, 100, &id[i]) == LBM_OK);
+    fail_at = allocs + k;
+    const lbm_status st = lbm_pool_run(P, 10);
+    const bool failed = allocs > fail_at;
+    fail_at = -1;
+    EXPECT((st != LBM_OK) == failed);
+    for (int i = 1; i < 3; ++i) EXPECT(lbm_pool_release(P, id[i]) == LBM_OK);
+    EXPECT(lbm_pool_run(P, 10) == LBM_OK);
+    EXPECT(lbm_pool_slot_time(P, id[0]) == (failed ? 20 : 30));
+    read_out(P, id[0], p);
+    EXPECT(lbm_pool_destroy(P) == LBM_OK);
+    EXPECT(blocks.empty());
+    return failed;
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "admission";
     int k = 0;
-    while ((what == "first" ? first(k) : admission(k)) && k < 100) ++k;
+    while ((what == "first" ? first(k) : what == "run" ? run_growth(k) : admission(k)) && k < 100) ++k;
     printf("%s: %d allocations failed in turn, %d failed expectations\n", what.c_str(), k, failures);
     return failures || k == 0;
 }

@@ -2,9 +2,9 @@
 
 tests/sanitize/pool_driver.cpp is a HIP runtime made of host memory and the
 library's host sources compiled with it under AddressSanitizer and
-UndefinedBehaviorSanitizer: every allocation that an admission makes fails in
-turn, and the slots admitted before it must still be stepped and read out
-through valid memory."""
+UndefinedBehaviorSanitizer: every allocation that an admission makes, or a run
+of more slots than before, fails in turn, and the slots admitted before it must
+still be stepped and read out through valid memory."""
 import os
 import shutil
 import subprocess
@@ -32,7 +32,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["first", "admission"])
+@pytest.mark.parametrize("what", ["first", "admission", "run"])
 def test_failed_allocation_leaves_the_pool_usable(driver, what):
     r = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True,
                        timeout=300)

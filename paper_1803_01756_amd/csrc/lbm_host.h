@@ -39,6 +39,10 @@ enum { kStatNonfinite = 0, kStatClamps = 1, kStatWords = lbmk::kStepWords };
 struct ReadoutMem {
     lbmk::Readout ro = {nullptr, nullptr};
     int cap = 0;  // workgroups it holds
+    // blocks it has grown out of, together no larger than the present one
+    // (each is at least twice the last, so 31 at most)
+    void* outgrown[31];
+    int n_outgrown = 0;
 };
 hipError_t reserve_readout(ReadoutMem& m, int Nx, int Ny);
 void free_readout(ReadoutMem& m);

@@ -1,4 +1,4 @@
-"""The pool's host code when an allocation fails (CPU only).
+"""The pool's host code around its allocations (CPU only).
 
 tests/sanitize/pool_driver.cpp is a HIP runtime made of host memory and the
 library's host sources compiled with it under AddressSanitizer and
@@ -32,9 +32,17 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["first", "admission", "run"])
-def test_failed_allocation_leaves_the_pool_usable(driver, what):
+def _run(driver, what):
     r = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True,
                        timeout=300)
     print(r.stdout)
     assert r.returncode == 0 and "0 failed expectations" in r.stdout, r.stdout
+
+
+@pytest.mark.parametrize("what", ["first", "admission", "run"])
+def test_failed_allocation_leaves_the_pool_usable(driver, what):
+    _run(driver, what)
+
+
+def test_admission_frees_nothing_while_the_batch_may_run(driver):
+    _run(driver, "growth")

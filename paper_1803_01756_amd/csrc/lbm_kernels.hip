@@ -505,10 +505,13 @@ struct RealOf<double> {
 // periods (exact: one fma), folded to a quarter turn either way, and the
 // Taylor series there (up to x^21 / 21!; the next term is below 2e-18).  A
 // call of sin() took half a microsecond of the one wave that evaluates it, and
-// the whole workgroup waits for that wave.
+// the whole workgroup waits for that wave.  Beyond 2^53 turns n / period is no
+// longer known to a turn and the first reduction leaves some over; the second
+// (exact, and nothing below half a turn) keeps the series to its range.
 __device__ double sin_of_period(long long n, double period, double inv_period) {
     const double t = (double)n;
     double a = __builtin_fma(-__builtin_rint(t * inv_period), period, t) * inv_period;
+    a -= __builtin_rint(a);
     if (fabs(a) > 0.25) a = copysign(0.5, a) - a;
     const double x = a * 6.283185307179586, z = x * x;
     double p = 1.0 / 51090942171709440000.0;

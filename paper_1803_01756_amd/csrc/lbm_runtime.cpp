@@ -603,8 +603,9 @@ void fill_phys(const lbm_params& p, Phys& k) {
     k.inv_Cv = 1.0 / p.C_v;
     k.lambda = p.lambda;
     k.g_osc = p.g_osc;
-    k.period = p.period;
-    k.inv_period = p.period > 0.0 ? 1.0 / p.period : 0.0;
+    // an infinite period stays at the sine's start: no drive, inlet at p0
+    k.period = std::isinf(p.period) ? 0.0 : p.period;
+    k.inv_period = k.period > 0.0 ? 1.0 / k.period : 0.0;
     k.g_x = p.g_x;
     k.g_y = p.g_y;
     k.rho_v = p.rho_v;
@@ -612,9 +613,10 @@ void fill_phys(const lbm_params& p, Phys& k) {
     if (p.flags & LBM_OPEN_X) {
         k.p0 = inlet_p0(p);
         inlet_bracket(p, &k.rho_sp, nullptr, nullptr);
-        k.p_amp = p.p_amp;
-        k.p_period = p.p_period;
-        k.inv_p_period = p.p_period > 0.0 ? 1.0 / p.p_period : 0.0;
+        const bool still = p.p_period > 0.0 && std::isinf(p.p_period);
+        k.p_amp = still ? 0.0 : p.p_amp;
+        k.p_period = still ? 0.0 : p.p_period;
+        k.inv_p_period = k.p_period > 0.0 ? 1.0 / k.p_period : 0.0;
         const Eos E = eos_of(p, p.T_c);
         const double T = inlet_temperature(p), ab = E.a * E.phi(T) / (E.b * E.b);
         k.in_e = E.cs ? 0.25 * E.b : E.b;

@@ -1210,12 +1210,11 @@ __device__ __forceinline__ int read_xp(const Grid& g, int cx) {
 // rows: each wave evaluates its own kReadRows rows (kept in registers but for
 // psi), the ring of one node around the block goes round in one more
 // evaluation by the first threads, and u follows from the psi in LDS.  The
-// outputs may be device memory or pinned host memory: a wave's stores of 64
-// consecutive doubles cross the link at the rate of the copy engine from some
-// 2 MB on (44 GB/s at 2.5 MB, 54 at 17, 56 at 134, the link's), and below that
-// one launch that writes the host arrays (13 us for 128 x 32) stands for a
-// clearing, two passes over the nodes with psi and j between them in memory,
-// and five copies (95 us).
+// outputs may be device memory or, for small results (ReadoutPlan), pinned host
+// memory: a wave's stores of 64 consecutive doubles cross the link at 44 GB/s at
+// 2.5 MB, 54 at 17, 56 at 134 (the link's rate), and one launch that writes the
+// host arrays (13 us for 128 x 32) stands for a clearing, two passes over the
+// nodes with psi and j between them in memory, and five copies (95 us).
 // Non-finite nodes are counted per workgroup into bad[], every entry written
 // on each launch, and the step's counters go along into words[]: both pinned
 // host memory, so that the read-out needs no copy of its own for them.

@@ -45,6 +45,7 @@ struct SlotState {
     int cur_f = 0, cur_T = 0;
     int64_t n = 0;           // time level after the work enqueued so far
     int64_t steps_left = 0;  // steps still to enqueue
+    int64_t chunk = 0;       // the last chunk it took part in (lbm_pool::chunks)
     int seg_rows = 0;        // rows of a segment of its launch shape
     bool ready_waited = false;
     bool reported = false;
@@ -117,6 +118,7 @@ struct lbm_pool {
     // device memory can stall the device while a batch runs)
     std::vector<std::pair<char*, size_t>> spare;
     int64_t steps_enqueued = 0;
+    int64_t chunks = 0;  // chunks enqueued
     // completion events of the chunks enqueued and not yet waited for
     std::vector<hipEvent_t> chunk_events, spare_events;
 };
@@ -457,9 +459,11 @@ lbm_status lbm_pool_run(lbm_pool* P, int32_t chunk) {
     for (int i = 0; i < longest; ++i)
         PCHK(lbmk::launch_step_batched(P->table_dev, (int)act.size(), blocks, tile, i, ext,
                                        P->main));
+    ++P->chunks;
     for (size_t j = 0; j < act.size(); ++j) {
         SlotState& s = P->slots[act[j]];
         const int take = (int)std::min<int64_t>(chunk, s.steps_left);
+        s.chunk = P->chunks;
         s.n += take;
         s.steps_left -= take;
         s.cur_f ^= (take & 1);
@@ -535,7 +539,12 @@ lbm_status lbm_pool_moments(lbm_pool* P, int32_t id, double* rho, double* ux, do
     if (st != LBM_OK) return st;
     double* const outs[4] = {rho, ux, uy, T};
     double* const dev[4] = {P->mom, P->mom + cells, P->mom + 2 * cells, P->mom + 3 * cells};
-    const lbmhost::ReadoutPlan plan = lbmhost::plan_readout(outs, dev, cells);
+    // steps of other slots that may still run when this slot's have ended
+    const bool beside = s->chunk != P->chunks && !P->chunk_events.empty() &&
+                        hipEventQuery(P->chunk_events.back()) != hipSuccess;
+    if (beside) (void)hipGetLastError();
+    const lbmhost::ReadoutPlan plan =
+        lbmhost::plan_readout(outs, dev, cells, beside ? 0 : lbmhost::kDirectPool);
     PCHK(lbmk::launch_moments_f32(s->g, s->k, s->f[s->cur_f], nullptr, s->T[s->cur_T],
                                   plan.direct, s->n, P->stat_dev + (size_t)id * kSlotStat,
                                   P->ro.ro, P->aux));

@@ -465,14 +465,16 @@ static double* pinned_view(double* p, size_t bytes) {
     return at <= size && bytes <= size - at ? static_cast<double*>(a.devicePointer) : nullptr;
 }
 
-ReadoutPlan plan_readout(double* const host[4], double* const dev[4], size_t cells) {
+ReadoutPlan plan_readout(double* const host[4], double* const dev[4], size_t cells, size_t direct) {
     ReadoutPlan r = {};
     double* to[4];
+    size_t bytes = 0;
+    for (int q = 0; q < 4; ++q) bytes += host[q] ? cells * sizeof(double) : 0;
     for (int q = 0; q < 4; ++q) {
         to[q] = nullptr;
         if (!host[q]) continue;
         // arrays that overlap are copied, so that the last one named stands
-        bool alone = true;
+        bool alone = bytes <= direct;
         for (int o = 0; o < 4; ++o)
             alone = alone && (o == q || !host[o] || host[o] + cells <= host[q] ||
                               host[q] + cells <= host[o]);
@@ -1000,7 +1002,8 @@ lbm_status lbm_moments(lbm_sim* s, double* rho, double* ux, double* uy, double* 
     double* const outs[4] = {rho, ux, uy, T};
     double* const dev[4] = {s->mom(0), s->mom(1), s->mom(2), s->mom(3)};
     const size_t cells = (size_t)s->p.Nx * s->p.Ny;
-    const lbmhost::ReadoutPlan plan = lbmhost::plan_readout(outs, dev, cells);
+    const lbmhost::ReadoutPlan plan =
+        lbmhost::plan_readout(outs, dev, cells, lbmhost::kDirectChannel);
     HIPCHK(enqueue_moments(s, plan.direct));
     HIPCHK(lbmhost::enqueue_copies(plan, cells, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));

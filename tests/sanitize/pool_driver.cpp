@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "lbm.h"
+#include "lbm_host.h"
 #include "lbm_internal.h"
 
 static int failures = 0;
@@ -42,6 +43,8 @@ struct Block {
 static std::map<char*, Block> blocks;
 static long allocs = 0, fail_at = -1, frees = 0;
 static hipError_t last = hipSuccess;
+static bool busy = false;             // the work enqueued last has not ended
+static lbmk::Moments told;            // where the last read-out's kernel wrote
 
 static const std::pair<char* const, Block>* find(const void* p) {
     auto it = blocks.upper_bound((char*)p);
@@ -97,7 +100,7 @@ hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return *e = (hipEv
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return busy ? result(hipErrorNotReady) : hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }
 hipError_t hipMemset(void* p, int v, size_t n) {
     EXPECT(holds(p, n));
@@ -146,6 +149,7 @@ hipError_t launch_moments_f32(const Grid& g, const Phys&, const float* f, const 
                     holds(ro.bad, nb * sizeof(unsigned));
     EXPECT(ok);
     if (!ok) return hipGetLastError();
+    told = out;
     double* const to[4] = {out.rho, out.ux, out.uy, out.T};
     for (int q = 0; q < 4; ++q) {
         if (!to[q]) continue;
@@ -292,13 +296,66 @@ static bool growth(int k) {
     return k < 1;
 }
 
+/* Who writes a read-out's pinned arrays: the kernel while no other slot's
+ * steps run beside it and the arrays are within the line, a copy otherwise. */
+static bool readout(int k) {
+    where = "readout";
+    const lbm_params p[2] = {channel(64, 20), channel(2048, 256)};  // the line: 16 MiB
+    const lbm_params above = channel(2049, 256);
+    lbm_pool* P = nullptr;
+    int32_t id[2], big;
+    EXPECT(lbm_pool_create((size_t)1 << 30, nullptr, &P) == LBM_OK);
+    for (int i = 0; i < 2; ++i) EXPECT(lbm_pool_admit(P, &p[i], nullptr, i ? 20 : 10, &id[i]) == LBM_OK);
+    EXPECT(lbm_pool_admit(P, &above, nullptr, 10, &big) == LBM_OK);
+    const auto direct = [&](int slot, const lbm_params& q) {
+        const size_t cells = (size_t)q.Nx * q.Ny;
+        void* mem = nullptr;
+        EXPECT(hipHostMalloc(&mem, 4 * cells * sizeof(double), 0) == hipSuccess);
+        double* a = static_cast<double*>(mem);
+        EXPECT(lbm_pool_moments(P, slot, a, a + cells, a + 2 * cells, a + 3 * cells) == LBM_OK);
+        for (int f = 0; f < 4; ++f)
+            EXPECT(a[f * cells] == 10.0 * q.Nx + f && a[(f + 1) * cells - 1] == 10.0 * q.Nx + f);
+        const bool d = told.rho == a;
+        EXPECT((told.ux == a + cells) == d && (told.T == a + 3 * cells) == d);
+        EXPECT(hipHostFree(mem) == hipSuccess);
+        return d;
+    };
+    EXPECT(lbm_pool_run(P, 10) == LBM_OK);
+    busy = true;  // its own chunk is the last one: nothing runs after it
+    EXPECT(direct(id[0], p[0]) && direct(id[1], p[1]) && !direct(big, above));
+    EXPECT(lbm_pool_run(P, 10) == LBM_OK);  // the second slot alone
+    EXPECT(!direct(id[0], p[0]) && direct(id[1], p[1]) && hipGetLastError() == hipSuccess);
+    busy = false;
+    EXPECT(direct(id[0], p[0]) && direct(id[1], p[1]));
+    EXPECT(lbm_pool_destroy(P) == LBM_OK);
+    // a channel's line, over the arrays that are asked for
+    void* mem = nullptr;
+    const size_t cells = ((size_t)4 << 20) / 32;
+    EXPECT(hipHostMalloc(&mem, 8 * cells * sizeof(double), 0) == hipSuccess);
+    double* a = static_cast<double*>(mem);
+    double dev[4];
+    double* const d[4] = {dev, dev + 1, dev + 2, dev + 3};
+    double* const four[4] = {a, a + cells, a + 2 * cells, a + 3 * cells};
+    double* const four1[4] = {a, a + cells + 1, a + 2 * cells + 2, a + 3 * cells + 3};
+    double* const two[4] = {a, nullptr, a + 2 * cells, nullptr};
+    const size_t line = lbmhost::kDirectChannel;
+    EXPECT(lbmhost::plan_readout(four, d, cells, line).direct.rho == a);
+    EXPECT(lbmhost::plan_readout(four1, d, cells + 1, line).direct.rho == dev);
+    EXPECT(lbmhost::plan_readout(two, d, 2 * cells, line).direct.uy == a + 2 * cells);
+    EXPECT(lbmhost::plan_readout(two, d, 2 * cells, line).direct.ux == nullptr);
+    EXPECT(hipHostFree(mem) == hipSuccess);
+    EXPECT(blocks.empty());
+    return k < 1;
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "admission";
     int k = 0;
-    while (k < 100 && (what == "first"    ? first(k)
-                       : what == "run"    ? run_growth(k)
-                       : what == "growth" ? growth(k)
-                                          : admission(k)))
+    while (k < 100 && (what == "first"     ? first(k)
+                       : what == "run"     ? run_growth(k)
+                       : what == "growth"  ? growth(k)
+                       : what == "readout" ? readout(k)
+                                           : admission(k)))
         ++k;
     printf("%s: %d turns, %d failed expectations\n", what.c_str(), k, failures);
     return failures || k == 0;

@@ -1,10 +1,11 @@
-"""The pool's host code around its allocations (CPU only).
+"""The pool's host code around its allocations and read-outs (CPU only).
 
 tests/sanitize/pool_driver.cpp is a HIP runtime made of host memory and the
 library's host sources compiled with it under AddressSanitizer and
 UndefinedBehaviorSanitizer: every allocation that an admission makes, or a run
 of more slots than before, fails in turn, and the slots admitted before it must
-still be stepped and read out through valid memory."""
+still be stepped and read out through valid memory; and a read-out's arrays are
+written by the kernel only where that holds up no steps."""
 import os
 import shutil
 import subprocess
@@ -46,3 +47,7 @@ def test_failed_allocation_leaves_the_pool_usable(driver, what):
 
 def test_admission_frees_nothing_while_the_batch_may_run(driver):
     _run(driver, "growth")
+
+
+def test_readout_beside_a_running_batch_is_copied(driver):
+    _run(driver, "readout")

@@ -100,6 +100,33 @@ struct Grid {
     unsigned plane;    // rows * pitch
 };
 
+// The tile of block `j` of a grid's g.n_blocks on XCD `xcd`.  Blocks are dealt
+// round-robin over the eight XCDs, each with its own L2.  A wide grid gives every
+// XCD a chunk of neighbouring strips and walks its rows chunk-width tiles at a
+// time, so that the tiles in flight on an XCD are a compact patch whose halos
+// meet in its L2, and all XCDs are on the same rows (HBM reads per step on
+// 8192 x 512: 176 MB against 235 for one row band per XCD, 88.9 us against
+// 93.9; fill_grid has the line).  A narrow grid gives every XCD a run of tiles in
+// row order, for the same shared halos (against tiles dealt one by one: 100 x 300
+// 7.4 us for 8.0, 1111 x 77 mass-exact 9.5 for 10.5, the pool of 20 76.2 for
+// 79.5).  down: the rows from the last to the first.  A channel's steps alternate:
+// the rows that a step wrote last are then read first, while the memory-side
+// cache still has them (84.8 against 88.4 us).
+__host__ __device__ inline bool tile_of_block(const Grid& g, int j, int xcd, bool down, int& strip,
+                                              int& seg) {
+    if (g.strips_per_xcd) {
+        const int i = j >> 3;
+        seg = i / g.strips_per_xcd;
+        strip = xcd * g.strips_per_xcd + (i - seg * g.strips_per_xcd);
+    } else {
+        const int i = xcd * (g.n_blocks >> 3) + (j >> 3);
+        seg = i / g.n_strips;
+        strip = i - seg * g.n_strips;
+    }
+    if (down) seg = g.n_segs - 1 - seg;
+    return strip < g.n_strips && seg >= 0 && seg < g.n_segs;
+}
+
 // Every buffer a step touches lies in one device allocation; the kernel
 // reaches them all through one buffer resource on `base`, by byte offsets.
 template <class S>
@@ -139,6 +166,17 @@ struct Slot {
     int block_begin;  // first workgroup of this slot in the batch
     unsigned long long* stat;  // the slot's health counters (see Bufs::stat)
 };
+
+// The block of the batch that workgroup `wg` of `n` takes at step `step_i` of a
+// chunk: odd steps take the batch from its end, for the same reason as a
+// channel's rows (tile_of_block), each slot's tiles from its end with them.  Its
+// XCD stays that of the workgroup, so that a tile meets the same L2 on every step.
+// (A pool of 20 channels 72.4 us per step and 64 channels 243.4 us; with the rows
+// of a slot turned round once more, so that only the slots' order alternated, 72.8
+// and 246.5; with neither 84.0 for the 20.)
+__host__ __device__ inline int batch_block(int wg, int n, int step_i) {
+    return (step_i & 1) ? n - 1 - wg : wg;
+}
 
 // Step i of a chunk over every slot of the table (slots sorted by
 // block_begin, total_blocks = sum of their workgroups), all with one tile shape.

@@ -1013,32 +1013,6 @@ __device__ __forceinline__ void step_tile(const Grid& g, const Phys& k, const Bu
     flush_health(B.stat, health);
 }
 
-// The tile of block `j` of a grid's g.n_blocks.  Blocks are dealt round-robin
-// over the eight XCDs, each with its own L2.  A wide grid gives every XCD a
-// chunk of neighbouring strips and walks its rows chunk-width tiles at a
-// time, so that the tiles in flight on an XCD are a compact patch whose halos
-// meet in its L2, and all XCDs are on the same rows (HBM reads per step on
-// 8192 x 512: 176 MB against 235 for one row band per XCD, 88.9 us against
-// 93.9; fill_grid has the line).  Steps alternate between walking the rows up and down: the rows a
-// step wrote last are then read first, while the memory-side cache still has
-// them (84.8 against 88.4 us).  A narrow grid gives every XCD a run of tiles in
-// row order, for the same shared halos (against tiles dealt one by one: 100 x 300
-// 7.4 us for 8.0, 1111 x 77 mass-exact 9.5 for 10.5, the pool of 20 76.2 for 79.5).
-__device__ __forceinline__ bool tile_of_block(const Grid& g, int j, long long n, int& strip,
-                                              int& seg) {
-    if (g.strips_per_xcd) {
-        const int i = j >> 3;
-        seg = i / g.strips_per_xcd;
-        strip = (j & 7) * g.strips_per_xcd + (i - seg * g.strips_per_xcd);
-    } else {
-        const int i = (j & 7) * (g.n_blocks >> 3) + (j >> 3);
-        seg = i / g.n_strips;
-        strip = i - seg * g.n_strips;
-    }
-    if (n & 1) seg = g.n_segs - 1 - seg;
-    return strip < g.n_strips && seg >= 0 && seg < g.n_segs;
-}
-
 // Reads one word of every 64-byte line of the step's constants, so that the
 // lines come into the scalar cache together at the start: read where they are
 // needed, each costs a trip to memory in its turn, some 13 in all (0.2 to
@@ -1062,7 +1036,7 @@ void step_kernel(Grid g, Phys k, Bufs<S> B, long long n) {
     touch_kernarg<sizeof(Grid) + sizeof(Phys) + sizeof(Bufs<S>) + sizeof(n)>();
     __shared__ TileLds<typename RealOf<S>::T, kWaves, kExt> L;
     int strip, seg;
-    if (!tile_of_block(g, blockIdx.x, n, strip, seg)) return;  // whole workgroups only
+    if (!tile_of_block(g, blockIdx.x, blockIdx.x & 7, n & 1, strip, seg)) return;  // whole workgroups only
     step_tile<S, kMX, kExt, kRows, kWaves>(g, k, B, n, strip, seg, L);
 }
 
@@ -1073,10 +1047,7 @@ template <bool kExt, int kRows, int kWaves, int kPerSimd>
 __global__ __launch_bounds__(kLanes* kWaves) __attribute__((amdgpu_waves_per_eu(kPerSimd)))
 void step_batched_kernel(const Slot* __restrict__ slots, int n_slots, int step_i) {
     __shared__ TileLds<float, kWaves, kExt> L;
-    // odd steps take the batch from its end, for the same reason as a channel's
-    // rows (tile_of_block): a pool of 20 channels 79.5 us per step for 84.0, 64
-    // channels 44.3 GLUPS for 42.4
-    const int block = (step_i & 1) ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
+    const int block = batch_block(blockIdx.x, gridDim.x, step_i);
     int lo = 0, hi = n_slots - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -1090,7 +1061,7 @@ void step_batched_kernel(const Slot* __restrict__ slots, int n_slots, int step_i
     const Phys k = sl.k;
     const long long n = sl.n0 + step_i;
     int strip, seg;
-    if (!tile_of_block(g, block - sl.block_begin, n, strip, seg)) return;
+    if (!tile_of_block(g, block - sl.block_begin, blockIdx.x & 7, false, strip, seg)) return;
     Bufs<float> B;
     B.base = sl.mem;
     B.span = sl.span;

@@ -348,6 +348,62 @@ static bool readout(int k) {
     return k < 1;
 }
 
+/* The order of a step's tiles: every tile is taken by exactly one workgroup,
+ * whatever the grid, alone on either kind of step and in a batch; a tile of a
+ * batch meets the same XCD on every step, and each XCD takes its tiles on odd
+ * steps in the reverse of the even ones' order. */
+static lbmk::Grid grid(int Nx, int Ny, int seg_rows, bool in_batch) {
+    const lbm_params p = channel(Nx, Ny);
+    lbmhost::Layout L;
+    lbmk::Grid g = {};
+    EXPECT(lbmhost::make_layout(p, &L));
+    lbmhost::fill_grid(p, L, seg_rows, lbmhost::tile_for(p, seg_rows), g, in_batch);
+    EXPECT(g.n_blocks % 8 == 0);
+    return g;
+}
+static bool order(int k) {
+    where = "order";
+    for (int strips = 1; strips <= 70; ++strips)
+        for (int rows : {2, 14, 15, 100})
+            for (int down = 0; down < 2; ++down) {
+                const lbmk::Grid g = grid(54 * strips, rows + 2, 14, false);
+                std::vector<int> taken(g.n_strips * g.n_segs, 0);
+                int strip, seg;
+                for (int b = 0; b < g.n_blocks; ++b)
+                    if (lbmk::tile_of_block(g, b, b & 7, down, strip, seg)) ++taken[seg * g.n_strips + strip];
+                for (int n : taken) EXPECT(n == 1);
+            }
+    const int sizes[][2] = {{64, 20}, {3000, 60}, {500, 100}, {55, 400}, {108, 31}};
+    std::vector<lbmk::Grid> g;
+    std::vector<int> begin;
+    int total = 0, tiles = 0;
+    for (auto& s : sizes) {
+        g.push_back(grid(s[0], s[1], 14, true));
+        begin.push_back(total);
+        total += g.back().n_blocks;
+        tiles += g.back().n_strips * g.back().n_segs;
+    }
+    std::vector<long> seen[2][8];  // tile numbers in the order an XCD takes them
+    for (int step = 0; step < 2; ++step) {
+        size_t n = 0;
+        for (int wg = 0; wg < total; ++wg) {
+            const int block = lbmk::batch_block(wg, total, step);
+            size_t slot = 0;
+            while (slot + 1 < g.size() && begin[slot + 1] <= block) ++slot;
+            int strip, seg;
+            if (!lbmk::tile_of_block(g[slot], block - begin[slot], wg & 7, false, strip, seg)) continue;
+            seen[step][wg & 7].push_back((long)slot * 1000000 + seg * 1000 + strip);
+            ++n;
+        }
+        EXPECT((int)n == tiles);
+    }
+    for (int x = 0; x < 8; ++x) {
+        std::vector<long> back(seen[1][x].rbegin(), seen[1][x].rend());
+        EXPECT(back == seen[0][x]);
+    }
+    return k < 1;
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "admission";
     int k = 0;
@@ -355,6 +411,7 @@ int main(int argc, char** argv) {
                        : what == "run"     ? run_growth(k)
                        : what == "growth"  ? growth(k)
                        : what == "readout" ? readout(k)
+                       : what == "order"   ? order(k)
                                            : admission(k)))
         ++k;
     printf("%s: %d turns, %d failed expectations\n", what.c_str(), k, failures);

@@ -51,3 +51,7 @@ def test_admission_frees_nothing_while_the_batch_may_run(driver):
 
 def test_readout_beside_a_running_batch_is_copied(driver):
     _run(driver, "readout")
+
+
+def test_every_tile_is_taken_once_in_the_stated_order(driver):
+    _run(driver, "order")

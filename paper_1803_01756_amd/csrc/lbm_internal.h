@@ -25,7 +25,8 @@ constexpr int kOwned = kLanes - 2 * kHalo;
 // rows (5 x 8) leave four waves per SIMD and measured 87.3 against Tall's 84.3.
 // Mass-exact storage keeps one FP64 density per row more: in Tall's 80
 // registers it spills three and writes 31 MB of them per step (8192 x 512: 104
-// us), so its tall tile is the 5 x 8 one (97.5; 4 x 8: 100.8).
+// us), so its tall tile is the 5 x 8 one (97.5; 4 x 8: 100.8).  Its Mid tile spills
+// three as well.
 // FP64: the halo exchange in LDS leaves one workgroup per CU.
 struct TileShape {
     int rows, waves, per_simd;

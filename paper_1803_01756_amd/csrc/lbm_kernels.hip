@@ -602,8 +602,8 @@ __device__ __forceinline__ double drive_at(const Phys& k, long long n) {
     return k.period > 0.0 ? k.g_osc * sin_of_period(n, k.period, k.inv_period) : 0.0;
 }
 
-// Add a wave's health word (see step_unit) to the counters: stat[0] gains
-// the number of lanes (node columns of the segment) that read a non-finite
+// Add a wave's health word (see step_tile) to the counters: stat[0] gains
+// the number of lanes (node columns of the wave's rows) that read a non-finite
 // value, stat[1] the clamped Eq. 10 arguments.  Called by every lane of the
 // wave; the sums and the atomics run only when some lane counted anything.
 __device__ __forceinline__ void flush_health(unsigned long long* stat, unsigned health) {
@@ -773,8 +773,8 @@ __device__ __forceinline__ void step_tile(const Grid& g, const Phys& k, const Bu
     const double rho_in = (open_x && __builtin_amdgcn_ballot_w64(at_in)) ? inlet_density(k, n) : 0.0;
     if (w == 0) L.drive = (R)drive_at(k, n);
     // health of the owned nodes (the state at level n), in one register:
-    // bits 0-30 count the Eq. 10 arguments clamped to psi = 0 (a lane owns
-    // fewer than 2^20 rows), bit 31 is set once the lane has read a
+    // bits 0-30 count the Eq. 10 arguments clamped to psi = 0 (at most one for
+    // each of the lane's kRows rows), bit 31 is set once the lane has read a
     // non-finite rho or T
     unsigned health = 0;
 

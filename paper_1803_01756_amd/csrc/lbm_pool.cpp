@@ -71,8 +71,10 @@ int row_bucket(int rows) {
     return b;
 }
 
-// Segments of about `target` rows, balanced over the slot's rows, with
-// seg + 10 (the halo rows) a multiple of 6, as the targets have it.
+// Segments of about `target` rows: the slot's rows in even parts, their height
+// rounded up so that seg + 10 (the halo rows) is a multiple of 6, as the targets
+// have it.  The last segment is the lower for it (158 rows in 26s: six of them
+// and one of 2), which keeps its spare waves idle.
 int balanced_seg_rows(int rows, int target) {
     int sr = lbmhost::balanced_rows(rows, target);
     sr = sr + (6 - (sr + 10) % 6) % 6;
@@ -91,7 +93,7 @@ struct lbm_pool {
     hipStream_t main = nullptr, aux = nullptr;
     bool owns_main = false;
     std::vector<SlotState> slots;
-    int seg_cap = 0;  // rows per wave in the batch (0: per-slot default)
+    int seg_cap = 0;  // rows of a segment in the batch (0: per-slot default)
     // tuned segment heights per bucket of fluid rows (lbm_pool_autotune;
     // 0: the default heuristic)
     int seg_target[kRowBuckets] = {};
@@ -182,7 +184,8 @@ lbm_status upload_density(lbm_pool* P, const double* rho0, double rho_v, size_t 
     return LBM_OK;
 }
 
-// Room for the counters of slot ids 0..n-1; a larger array is filled from the old one while no stream uses it.
+// Room for the counters of slot ids 0..n-1; a larger array is filled from the
+// old one while no stream uses it.
 lbm_status ensure_stat(lbm_pool* P, int n) {
     if (n <= P->stat_cap) return LBM_OK;
     PCHK(hipStreamSynchronize(P->main));
@@ -219,8 +222,15 @@ SlotState* get_slot(lbm_pool* P, int32_t id) {
     return &P->slots[id];
 }
 
-// Default segment height of a batch of slots: the line between the Mid and
-// the Tall tile lies where it does for a channel alone (default_tile).
+// Default segment height of a batch of slots: the line between the Mid and the
+// Tall tile lies where it does for a plain channel alone (default_tile), with
+// optional features too.  Between 1024 tall tiles, such a channel's own line, and
+// 2048 either tile is the shorter by up to 5 % for a batch with them, as the
+// slots' last rounds fall (us, Mid / Tall): gravity plates of 1000 x 200, seven
+// 41.4 / 42.5, eight 45.8 / 43.5, nine 52.5 / 49.9; of 1000 x 300, six 49.3 / 49.6,
+// eight 64.4 / 63.3; boxes of 400, 500 and 1000 a side 44.4 / 45.4.  The Flat tile
+// is no batch's default (128 x 32, 200 x 50 and 64 x 20 together 7.9 us in Mid
+// tiles, 6.3 in Flat ones; six channels of some 300 x 60 10.1 / 10.6).
 int default_target(const lbm_pool* P, const std::vector<int>& slots) {
     const int tall = lbmk::kTiles[lbmk::kTileTall].own();
     long long tiles = 0;

@@ -526,10 +526,16 @@ int default_tile(const lbm_params& p, int rows) {
         return tiles(lbmk::kTileTall64) <= 1024 ? lbmk::kTileMid64 : lbmk::kTileTall64;
     }
     if (tiles(lbmk::kTileFlat) <= 512) return lbmk::kTileFlat;
-    // The FP32 build with the optional features fits two Mid workgroups or one
-    // Tall one on a CU, and Tall wins earlier: with gravity and mixed plates
-    // 4096 x 256 (760 tall tiles) in 31.6 (Mid) against 31.9, 3000 x 512 (1120)
-    // 44.3 / 42.0, 4096 x 512 55.8 / 52.8.
+    // With the optional features Tall wins earlier in FP32: that build keeps as
+    // many workgroups on a CU (80 VGPRs for 77) but spends more on every row, the
+    // halo's too: with gravity and mixed plates 4096 x 256 (760 tall tiles) in
+    // 31.0 (Mid) against 31.8, 3000 x 512 (1120) 41.3 / 40.5, 4096 x 512 55.8 /
+    // 52.8.  Its Flat tile fits a CU once, not twice (73 VGPRs for 46), so from
+    // 257 flat tiles to 512 Mid would be the shorter by 4 to 14 % (box 285 x 285
+    // 13.9 Flat, 13.2 Mid; gravity 200 x 600 14.4 / 12.6; 1600 x 48 with open ends,
+    // 240 tiles, 9.6 / 13.1).  Mass-exact storage keeps the plain line, though its
+    // tall tile is another and its Mid tile spills three registers: 2048 x 256
+    // 16.2 (Mid) / 18.4, 4096 x 512 46.0 / 45.2, 8192 x 512 110.0 / 97.8.
     const bool ext = (p.flags & (LBM_FRAME_T | LBM_FRAME_RHO | LBM_EOS_CS | LBM_OPEN_X |
                                  LBM_PHASE_PROPS | LBM_TOP_MIXED)) ||
                      p.T_w_end > 0.0 || p.alpha_max > 0.0;
@@ -572,12 +578,16 @@ void fill_grid(const lbm_params& p, const Layout& L, int seg_rows, int tile, Gri
     g.seg_rows = balanced_rows(std::max(1, std::min(seg_rows, g.rows)), lbmk::kTiles[tile].own());
     g.n_strips = strips_of(p);
     g.n_segs = (g.rows + g.seg_rows - 1) / g.seg_rows;
-    // chunks of strips per XCD only where the last one is not left nearly idle
-    // Chunks of columns for the XCDs from four strips each on: with runs of
-    // tiles instead 2048 x 256 (38 strips) takes 15.8 us for 15.3, 3400 x 512
-    // (63) 37.1 for 33.1.  In a batch every slot takes runs: chunks leave the
-    // XCDs of a slot with unequal work (a pool of 20 channels 76.1 us for
-    // 73.4, 64 channels 45.4 GLUPS for 46.5).
+    // A channel alone deals chunks of ceil(strips / 8) strips to the XCDs from 32
+    // strips on, runs of tiles below.  The last chunk may be narrow, or empty (at
+    // 33 to 35, 41, 42 and 49 strips), and chunks are still the shorter on low
+    // grids, where a step is a round or two of tiles either way (us, chunks / runs):
+    // 33 strips x 126 rows 11.1 / 13.9, x 254 14.4 / 16.0; 36 x 254 14.4 / 15.4; 41 x
+    // 254 17.1 / 17.8; 49 x 254 18.1 / 18.1; 63 x 510 32.8 / 36.2; 152 x 510 85.4 /
+    // 91.9.  Where the fullest XCD takes a round more for it, runs would be: 33 x
+    // 510 23.2 / 21.4, 41 x 510 25.8 / 24.5, 41 x 254 in FP64 35.6 / 29.4.  In a batch
+    // every slot takes runs: chunks leave the XCDs of a slot with unequal work
+    // (a pool of 20 channels 76.1 us for 73.4, 64 channels 45.4 GLUPS for 46.5).
     g.strips_per_xcd = !in_batch && g.n_strips >= 32 ? (g.n_strips + 7) / 8 : 0;
     g.n_blocks = g.strips_per_xcd ? 8 * g.strips_per_xcd * g.n_segs
                                   : (g.n_strips * g.n_segs + 7) / 8 * 8;

@@ -55,14 +55,15 @@ unsigned long long readout_bad(const ReadoutMem& m, int Nx, int Ny);
 // the device array that stands for it.  The kernel's stores to the host hold up
 // whatever else the GPU runs until the link has taken them (a smaller grid of
 // workgroups does not help), a copy does not.  Alone the kernel is the faster of
-// the two up to some 16 MiB (128 x 32 23 us for 57, 1024 x 128 96 for 135, 2048 x
-// 256 335 for 363, 4096 x 512 1283 for 1273, 8192 x 512 2545 for 2485); beside
-// steps on another stream each read-out costs them 20 us for 4 (200 x 200), 72
-// for 5 (1024 x 128: 4 MiB) and 1300 for 48 (4096 x 512: 64 MiB).  A channel does
-// not know what else the GPU runs: its line is 4 MiB, up to where the caller
-// gains what others lose against two passes and five copies (96 and 72 us for
-// 165 and 7).  A pool knows its own batch: 16 MiB while no chunk is left running
-// beside the slot's own, else nothing.
+// the two up to some 16 MiB (us, kernel / one copy of four adjoining arrays / four
+// copies: 128 x 32 23 / 33 / 57, 200 x 200 45 / 55 / 79, 1024 x 128 96 / 110 / 135,
+// 2048 x 256 331 / 337 / 363, 4096 x 512 1282 / 1247 / 1273, 8192 x 512 2545 / 2455 /
+// 2485); beside steps on another stream a read-out costs them 20 us for 2 (200 x
+// 200), 73 for 4 (1024 x 128: 4 MiB), 308 for 16 (2048 x 256) and 1294 for 40 (4096 x
+// 512).  A channel does not know what else the GPU runs: its line is 4 MiB, up to
+// where the caller gains what others lose against two passes and five copies (96
+// and 73 us for 160 and 7).  A pool knows its own batch: 16 MiB while no chunk is
+// left running beside the slot's own, else nothing.
 constexpr size_t kDirectChannel = (size_t)4 << 20, kDirectPool = (size_t)16 << 20;
 struct ReadoutPlan {
     lbmk::Moments direct;  // what the kernel writes

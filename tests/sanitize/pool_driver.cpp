@@ -45,6 +45,7 @@ static long allocs = 0, fail_at = -1, frees = 0;
 static hipError_t last = hipSuccess;
 static bool busy = false;             // the work enqueued last has not ended
 static lbmk::Moments told;            // where the last read-out's kernel wrote
+static int copies = 0;                // device to host
 
 static const std::pair<char* const, Block>* find(const void* p) {
     auto it = blocks.upper_bound((char*)p);
@@ -113,6 +114,7 @@ hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind kind) {
                     (kind == hipMemcpyHostToDevice || holds(s, n));
     EXPECT(ok);
     if (ok) memmove(d, s, n);
+    copies += kind == hipMemcpyDeviceToHost;
     return ok ? hipSuccess : result(hipErrorInvalidValue);
 }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind kind, hipStream_t) {
@@ -348,6 +350,42 @@ static bool readout(int k) {
     return k < 1;
 }
 
+/* Copies of a read-out: one for arrays that follow one another in a pinned
+ * allocation, one each where they do not, where the run of them leaves its
+ * allocation for one that happens to adjoin, or in memory that is not pinned. */
+static bool merge(int k) {
+    where = "merge";
+    const size_t cells = 1000, bytes = cells * sizeof(double);
+    double* dev = nullptr;
+    double* pin = nullptr;
+    EXPECT(hipMalloc((void**)&dev, 4 * bytes) == hipSuccess && hipHostMalloc((void**)&pin, 5 * bytes, 0) == hipSuccess);
+    for (size_t i = 0; i < 4 * cells; ++i) dev[i] = (double)i;
+    double* const d[4] = {dev, dev + cells, dev + 2 * cells, dev + 3 * cells};
+    const auto run = [&](double* a, double* b, double* c, double* e) {
+        double* const to[4] = {a, b, c, e};
+        memset(pin, 0, 5 * bytes);
+        const int before = copies;
+        EXPECT(lbmhost::enqueue_copies(lbmhost::plan_readout(to, d, cells, 0), cells, nullptr) == hipSuccess);
+        for (int q = 0; q < 4; ++q)
+            if (to[q]) EXPECT(memcmp(to[q], d[q], bytes) == 0);
+        return copies - before;
+    };
+    double* const p = pin;
+    EXPECT(run(p, p + cells, p + 2 * cells, p + 3 * cells) == 1);
+    EXPECT(run(p, p + cells, p + 2 * cells + 1, p + 3 * cells + 1) == 2);
+    EXPECT(run(p + cells, p, p + 3 * cells, p + 2 * cells) == 4);
+    EXPECT(run(p, nullptr, p + 2 * cells, p + 3 * cells) == 2);
+    EXPECT(run(nullptr, nullptr, nullptr, p) == 1 && run(nullptr, nullptr, nullptr, nullptr) == 0);
+    std::vector<double> page(4 * cells);
+    EXPECT(run(&page[0], &page[cells], &page[2 * cells], &page[3 * cells]) == 4);
+    blocks[(char*)p].bytes = 2 * bytes;  // split into two that adjoin
+    blocks[(char*)(p + 2 * cells)] = {3 * bytes, true};
+    EXPECT(run(p, p + cells, p + 2 * cells, p + 3 * cells) == 3);  // two in the second
+    blocks.erase((char*)(p + 2 * cells));
+    EXPECT(hipHostFree(pin) == hipSuccess && hipFree(dev) == hipSuccess && blocks.empty());
+    return k < 1;
+}
+
 /* The order of a step's tiles: every tile is taken by exactly one workgroup,
  * whatever the grid, alone on either kind of step and in a batch; a tile of a
  * batch meets the same XCD on every step, and each XCD takes its tiles on odd
@@ -411,6 +449,7 @@ int main(int argc, char** argv) {
                        : what == "run"     ? run_growth(k)
                        : what == "growth"  ? growth(k)
                        : what == "readout" ? readout(k)
+                       : what == "merge"   ? merge(k)
                        : what == "order"   ? order(k)
                                            : admission(k)))
         ++k;

@@ -53,5 +53,9 @@ def test_readout_beside_a_running_batch_is_copied(driver):
     _run(driver, "readout")
 
 
+def test_adjoining_pinned_arrays_are_copied_at_once(driver):
+    _run(driver, "merge")
+
+
 def test_every_tile_is_taken_once_in_the_stated_order(driver):
     _run(driver, "order")

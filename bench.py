@@ -47,7 +47,7 @@ def pmc_file(tag):
 # the sources that decide what a step launch reads and writes: the kernels and
 # the device layout (plane stride, pitch, buffer offsets)
 TRAFFIC_SRCS = [os.path.join(ROOT, "paper_1803_01756_amd", "csrc", f)
-                for f in ("lbm_kernels.hip", "lbm_runtime.cpp", "lbm_host.h")]
+                for f in ("lbm_kernels.hip", "lbm_runtime.cpp", "lbm_host.h", "lbm_internal.h")]
 
 
 def log(msg):
@@ -146,10 +146,10 @@ def run_config(p, rho0, steps, warmup, tune=True, seg_rows=0):
         sim.autotune(10)
     preheat(sim)
     ms, wall_ms = time_steps(sim, steps, warmup)
-    seg, waves = sim.launch()
+    seg, segments = sim.launch()
     red = sim.reduce(check=False)
     sim.close()
-    return ms, wall_ms, seg, waves, red
+    return ms, wall_ms, seg, segments, red
 
 
 def oracle_mlups(p, rho0, steps, omp=False):
@@ -201,7 +201,7 @@ def batch_and_serve(args):
                    sims_per_s=round(64 / tb, 3),
                    launch="lbm_pool_autotune (per bucket of fluid rows)",
                    tuned_ms_per_step=round(info["tuned_ms_per_step"], 4),
-                   waves_per_step=sum(w for _, w in info["shapes"]),
+                   segments_per_step=sum(n for _, n in info["shapes"]),
                    seg_rows_min_median_max=[min(seg), int(np.median(seg)), max(seg)],
                    default_policy_seconds=round(tb0, 4),
                    default_policy_mlups=round(lups / tb0 / 1e6, 1),
@@ -594,7 +594,7 @@ def main():
     n = fluid_nodes(p)
     log("8192x512 %s: tune + %.2f s of untimed steps + %d warmup + %d timed steps"
         % (args.precision, PREHEAT_S, args.warmup, args.steps))
-    ms, wall_ms, seg, waves, red = run_config(p, rho0, args.steps, args.warmup,
+    ms, wall_ms, seg, segments, red = run_config(p, rho0, args.steps, args.warmup,
                                               tune=not args.no_tune, seg_rows=args.seg_rows)
     ms_step = ms / args.steps
     mlups = n * args.steps / (ms * 1e-3) / 1e6
@@ -662,7 +662,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": "plate channel 8192x512, %s, Tw=0.78Tc, "
                                "75 deg wall, drive 2e-6 / 4000 steps, seeded vapour noise" % storage,
-                   "Nx": p.Nx, "Ny": p.Ny, "fluid_nodes": n, "seg_rows": seg, "waves": waves,
+                   "Nx": p.Nx, "Ny": p.Ny, "fluid_nodes": n, "seg_rows": seg, "segments": segments,
                    "untimed_preheat_s": PREHEAT_S},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),

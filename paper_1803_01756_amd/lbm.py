@@ -389,7 +389,8 @@ class Sim:
         lbm_set_launch(self.h, seg_rows)
 
     def launch(self):
-        """(seg_rows, waves) of the current launch shape (lbm_get_launch)."""
+        """(rows of a segment, segments of a step) of the current launch shape
+        (lbm_get_launch)."""
         return lbm_get_launch(self.h)
 
     def autotune(self, steps_per_trial: int = 10) -> float:
@@ -500,7 +501,7 @@ class Pool:
         return ms.value
 
     def slot_launch(self, slot: int):
-        """(rows of a segment, tiles per step) of a slot."""
+        """(rows of a segment, segments of a step) of a slot."""
         sr, w = C.c_int32(), C.c_int32()
         _check(lib().lbm_pool_slot_launch(C.c_void_p(self.h), int(slot), C.byref(sr),
                                           C.byref(w)))

@@ -127,7 +127,7 @@ def run_alone(channels, steps: int, keep_results: bool = False, tune_steps: int 
               shapes: list = None):
     """The same channels one after another with lbm_create/lbm_step;
     tune_steps > 0: each is autotuned first (lbm_autotune, untimed), and
-    `shapes` receives each one's (rows of a segment, tiles)."""
+    `shapes` receives each one's (rows of a segment, segments)."""
     total = 0.0
     res = []
     for p, rho0 in channels:

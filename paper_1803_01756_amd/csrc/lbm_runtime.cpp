@@ -951,8 +951,9 @@ lbm_status lbm_create(const lbm_params* pin, const double* rho0, void* workspace
     } else {
         e = hipMalloc(reinterpret_cast<void**>(&s->base), s->L.total);
         if (e != hipSuccess) {
+            const size_t total = s->L.total;
             delete s;
-            return fail(LBM_ENOMEM, "hipMalloc(%zu): %s", s->L.total, hipGetErrorString(e));
+            return fail(LBM_ENOMEM, "hipMalloc(%zu): %s", total, hipGetErrorString(e));
         }
         s->owns_mem = true;
     }

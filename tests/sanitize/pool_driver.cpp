@@ -278,6 +278,21 @@ static bool run_growth(int k) {
     return failed;
 }
 
+/* A channel's creation without memory. */
+static bool create(int k) {
+    where = "create " + std::to_string(k);
+    const lbm_params p = channel(300, 90);
+    lbm_sim* s = nullptr;
+    fail_at = allocs + k;
+    const lbm_status st = lbm_create(&p, nullptr, nullptr, 0, nullptr, &s);
+    const bool failed = allocs > fail_at;
+    fail_at = -1;
+    EXPECT(st == (failed ? LBM_ENOMEM : LBM_OK) && (s == nullptr) == failed);
+    EXPECT(lbm_destroy(s) == LBM_OK && blocks.empty());
+    (void)hipGetLastError();
+    return failed;
+}
+
 /* Freeing memory waits for the device, so an admission that the moment
  * arrays have room for frees nothing, though its read-out takes more
  * workgroups than any before (65 x 57 against 64 x 64 nodes). */
@@ -449,6 +464,7 @@ int main(int argc, char** argv) {
                        : what == "run"     ? run_growth(k)
                        : what == "growth"  ? growth(k)
                        : what == "readout" ? readout(k)
+                       : what == "create"  ? create(k)
                        : what == "merge"   ? merge(k)
                        : what == "order"   ? order(k)
                                            : admission(k)))

@@ -45,6 +45,10 @@ def test_failed_allocation_leaves_the_pool_usable(driver, what):
     _run(driver, what)
 
 
+def test_creation_without_memory(driver):
+    _run(driver, "create")
+
+
 def test_admission_frees_nothing_while_the_batch_may_run(driver):
     _run(driver, "growth")
 

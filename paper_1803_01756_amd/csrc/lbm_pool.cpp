@@ -25,10 +25,8 @@ namespace {
 #define PCHK(expr)                                                                        \
     do {                                                                                  \
         hipError_t e_ = (expr);                                                           \
-        if (e_ != hipSuccess) {                                                           \
-            (void)hipGetLastError(); /* or the next launch would report it again */       \
+        if (e_ != hipSuccess)                                                             \
             return fail(LBM_EDEVICE, "%s failed: %s", #expr, hipGetErrorString(e_));      \
-        }                                                                                 \
     } while (0)
 
 struct SlotState {
@@ -201,7 +199,6 @@ lbm_status ensure_stat(lbm_pool* P, int n) {
         e = hipMemcpy(d, P->stat_dev, (size_t)P->stat_cap * kSlotStat * sizeof(*d),
                       hipMemcpyDeviceToDevice);
     if (e != hipSuccess) {
-        (void)hipGetLastError();
         (void)hipFree(d);
         if (h) (void)hipHostFree(h);
         return fail(LBM_EDEVICE, "health counters: %s", hipGetErrorString(e));
@@ -351,7 +348,6 @@ lbm_status lbm_pool_admit(lbm_pool* P, const lbm_params* pin, const double* rho0
             e = hipMalloc(reinterpret_cast<void**>(&s.mem), need);
         }
         if (e != hipSuccess) {
-            (void)hipGetLastError();
             s = SlotState();
             return fail(LBM_ENOMEM, "slot allocation of %zu bytes failed", need);
         }
@@ -694,7 +690,6 @@ lbm_status lbm_pool_autotune(lbm_pool* P, int32_t steps_per_trial, double* best_
     total += act.size() * sizeof(lbmk::Slot);
     char* shadow = nullptr;
     if (hipMalloc(reinterpret_cast<void**>(&shadow), total) != hipSuccess) {
-        (void)hipGetLastError();
         return fail(LBM_ENOMEM, "autotune: no room for the %zu-byte trial copy", total);
     }
     std::vector<lbmk::Slot> tab(act.size());

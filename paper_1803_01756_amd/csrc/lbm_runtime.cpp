@@ -32,6 +32,9 @@ lbm_status fail(lbm_status st, const char* fmt, ...) {
     va_start(ap, fmt);
     vsnprintf(g_err, sizeof(g_err), fmt, ap);
     va_end(ap);
+    // a HIP error reported here stays the thread's last one until it is taken,
+    // and the next launch, of any channel, would report it again
+    if (st == LBM_EDEVICE || st == LBM_ENOMEM) (void)hipGetLastError();
     return st;
 }
 
@@ -971,7 +974,6 @@ lbm_status lbm_create(const lbm_params* pin, const double* rho0, void* workspace
     set_grid(s, 0);
     e = lbmhost::reserve_readout(s->ro, p.Nx, p.Ny);
     if (e != hipSuccess) {
-        (void)hipGetLastError();
         lbm_destroy(s);
         return fail(LBM_ENOMEM, "pinned host memory: %s", hipGetErrorString(e));
     }

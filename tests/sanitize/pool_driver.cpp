@@ -173,11 +173,14 @@ hipError_t launch_step_batched(const Slot* slots, int n, int, int, int, bool, hi
     EXPECT(holds(slots, n * sizeof(Slot)));
     return hipGetLastError();
 }
-/* not reached by a pool */
+hipError_t launch_step_f32(const Grid&, const Phys&, const Bufs<float>& b, bool, int64_t, hipStream_t) {
+    EXPECT(holds(b.base, b.span));
+    return hipGetLastError();
+}
+/* not reached here */
 hipError_t launch_init_f64(const Grid&, const Phys&, const double*, double*, double*, hipStream_t) { abort(); }
 hipError_t launch_moments_f64(const Grid&, const Phys&, const double*, const double*, const Moments&, int64_t,
                               const unsigned long long*, const Readout&, hipStream_t) { abort(); }
-hipError_t launch_step_f32(const Grid&, const Phys&, const Bufs<float>&, bool, int64_t, hipStream_t) { abort(); }
 hipError_t launch_step_f64(const Grid&, const Phys&, const Bufs<double>&, int64_t, hipStream_t) { abort(); }
 hipError_t launch_reduce(const double*, const double*, const double*, const double*, int, double, double*,
                          double*, hipStream_t) { abort(); }
@@ -185,7 +188,10 @@ hipError_t launch_reduce_state_f32(const Grid&, const Phys&, const float*, const
                                    int64_t, double*, hipStream_t) { abort(); }
 hipError_t launch_reduce_state_f64(const Grid&, const Phys&, const double*, const double*, double, int64_t,
                                    double*, hipStream_t) { abort(); }
-hipError_t launch_copy(const void*, void*, size_t, hipStream_t) { abort(); }
+hipError_t launch_copy(const void* s, void* d, size_t n, hipStream_t) {
+    EXPECT(holds(s, n) && holds(d, n));
+    return hipGetLastError();
+}
 }  // namespace lbmk
 
 /* ---- the checks ------------------------------------------------------------------ */
@@ -291,6 +297,37 @@ static bool create(int k) {
     EXPECT(lbm_destroy(s) == LBM_OK && blocks.empty());
     (void)hipGetLastError();
     return failed;
+}
+
+/* A channel while another's creation, its tuning or the bandwidth probe finds
+ * no memory: its next step and read-out are not told of it. */
+static bool channel_calls(int k) {
+    where = "channel " + std::to_string(k);
+    const lbm_params p = channel(64, 20), q = channel(300, 90);
+    const auto failing = [&](auto call) {
+        lbm_sim* s = nullptr;
+        EXPECT(lbm_create(&p, nullptr, nullptr, 0, nullptr, &s) == LBM_OK);
+        fail_at = allocs + k;
+        const lbm_status st = call(s);
+        const bool failed = allocs > fail_at;
+        fail_at = -1;
+        EXPECT((st != LBM_OK) == failed);
+        EXPECT(lbm_step(s, 2) == LBM_OK);
+        std::vector<double> T((size_t)p.Nx * p.Ny);
+        EXPECT(lbm_moments(s, nullptr, nullptr, nullptr, T.data()) == LBM_OK && T.back() == 10.0 * p.Nx + 3);
+        EXPECT(lbm_destroy(s) == LBM_OK && blocks.empty());
+        return failed;
+    };
+    bool any = failing([&](lbm_sim*) {
+        lbm_sim* o = nullptr;
+        const lbm_status st = lbm_create(&q, nullptr, nullptr, 0, nullptr, &o);
+        EXPECT((o != nullptr) == (st == LBM_OK));
+        EXPECT(lbm_destroy(o) == LBM_OK);
+        return st;
+    });
+    any |= failing([](lbm_sim* s) { return lbm_autotune(s, 2, nullptr); });
+    any |= failing([](lbm_sim*) { return lbm_bandwidth_probe(1 << 20, 2, nullptr, nullptr); });
+    return any;
 }
 
 /* Freeing memory waits for the device, so an admission that the moment
@@ -465,6 +502,7 @@ int main(int argc, char** argv) {
                        : what == "growth"  ? growth(k)
                        : what == "readout" ? readout(k)
                        : what == "create"  ? create(k)
+                       : what == "channel" ? channel_calls(k)
                        : what == "merge"   ? merge(k)
                        : what == "order"   ? order(k)
                                            : admission(k)))

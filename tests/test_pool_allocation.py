@@ -49,6 +49,10 @@ def test_creation_without_memory(driver):
     _run(driver, "create")
 
 
+def test_failed_allocation_is_not_reported_by_another_channel(driver):
+    _run(driver, "channel")
+
+
 def test_admission_frees_nothing_while_the_batch_may_run(driver):
     _run(driver, "growth")
 

@@ -1,5 +1,6 @@
-/* The slot pool's host code on a HIP runtime made of host memory, with every
- * allocation of an admission or a run failing in turn.
+/* The library's host code on a HIP runtime made of host memory, with every
+ * allocation of a call failing in turn; who writes a read-out's arrays; and the
+ * order of a step's tiles.
  *
  * The HIP calls that lbm_runtime.cpp and lbm_pool.cpp make are defined here:
  * device and pinned memory come from malloc and are kept in a table, copies

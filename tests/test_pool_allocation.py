@@ -1,11 +1,12 @@
-"""The pool's host code around its allocations and read-outs (CPU only).
+"""The host code around allocations, read-outs and launch order (CPU only).
 
 tests/sanitize/pool_driver.cpp is a HIP runtime made of host memory and the
 library's host sources compiled with it under AddressSanitizer and
-UndefinedBehaviorSanitizer: every allocation that an admission makes, or a run
-of more slots than before, fails in turn, and the slots admitted before it must
-still be stepped and read out through valid memory; and a read-out's arrays are
-written by the kernel only where that holds up no steps."""
+UndefinedBehaviorSanitizer: every allocation that an admission, a run of more
+slots than before, a channel's creation or its tuning makes fails in turn, and
+what was there before must still be stepped and read out through valid memory; a
+read-out's arrays are written by the kernel only where that holds up no steps;
+and every tile of a step is taken once, in the stated order."""
 import os
 import shutil
 import subprocess
